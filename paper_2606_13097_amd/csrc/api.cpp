@@ -363,21 +363,34 @@ void stage_pages(fcg_cache* c, const std::vector<std::pair<int32_t, int32_t>>& n
   for (int32_t s : seqs) rows->push_back({s, stage_row(c, s, blob)});
 }
 
-// Upload the blob; copy page rows into the device page table.  *dev receives
-// the device address of the blob.
+// Upload a plan: the staged page rows (at the front of the blob, in the order
+// staged) into the device page table, the rest of the blob into the device ring,
+// both read by one small kernel from the pinned ring.  *dev and *off_out receive
+// the blob's place in the device ring.
 fcg_status upload(fcg_cache* c, const Blob& blob, const std::vector<std::pair<int32_t, size_t>>& rows,
                   hipStream_t s, char** dev, size_t* off_out) {
-  size_t n = std::max<size_t>(blob.bytes.size(), 256), off;
+  const size_t n = std::max<size_t>((blob.bytes.size() + 255) & ~size_t(255), 256);
+  size_t off;
   fcg_status st = c->ring.acquire(n, &off);
   if (st) return st;
   std::memcpy(c->ring.host + off, blob.bytes.data(), blob.bytes.size());
-  HIP_TRY(hipMemcpyAsync(c->ring.dev + off, c->ring.host + off, blob.bytes.size(), hipMemcpyHostToDevice, s),
-          "hipMemcpyAsync(plan)");
-  const size_t nlp = c->plan.n_logical_pages();
-  for (auto& r : rows)
-    HIP_TRY(hipMemcpyAsync(c->d_page_table + (size_t)r.first * 2 * nlp, c->ring.dev + off + r.second,
-                           2 * nlp * sizeof(int32_t), hipMemcpyDeviceToDevice, s),
-            "hipMemcpyAsync(page table)");
+  const size_t row_bytes = 2 * (size_t)c->plan.n_logical_pages() * sizeof(int32_t);
+  const size_t stride = (row_bytes + 255) & ~size_t(255);
+  const size_t from = std::min(rows.size() * stride, n);  // the rows are staged first, one aligned member each
+  UploadArgs a{};
+  a.host = c->ring.host + off + from;
+  a.dev = c->ring.dev + off + from;
+  a.bytes = blob.bytes.size() > from ? (int64_t)((blob.bytes.size() - from + 15) & ~size_t(15)) : 0;
+  a.row_stride = (int64_t)stride;
+  a.page_table = c->d_page_table;
+  a.row_ints = (int32_t)(row_bytes / sizeof(int32_t));
+  for (size_t r0 = 0; r0 == 0 || r0 < rows.size(); r0 += kUploadRows) {
+    a.rows = c->ring.host + off + r0 * stride;
+    a.n_rows = (int32_t)std::min<size_t>(kUploadRows, rows.size() - r0);
+    for (int32_t i = 0; i < a.n_rows; ++i) a.seq[i] = rows[r0 + i].first;
+    if (int rc = launch_upload(a, s)) return hip_fail((hipError_t)rc, "plan upload launch");
+    a.bytes = 0;
+  }
   *dev = c->ring.dev + off;
   *off_out = off;
   return FCG_OK;
@@ -886,27 +899,47 @@ fcg_status fcg_graft(fcg_cache* c, const fcg_lib* lib, int32_t n_items, const in
   Blob blob;
   std::vector<std::pair<int32_t, size_t>> rows;
   stage_pages(c, new_pages, &blob, &rows);
+  // up to kGraftArgItems segments in kGraftArgRuns runs go by value, and
+  // nothing is uploaded unless the call maps pages; longer lists go through the
+  // staging ring
+  int64_t n_runs = 0;
+  for (auto& sp : spans) n_runs += (sp.len + kGraftChunk - 1) / kGraftChunk;
+  const bool by_value = n_items <= kGraftArgItems && n_runs <= kGraftArgRuns;
+  GraftArgs args;
   std::vector<GraftChunk> chunks;
-  for (auto& sp : spans) {
-    const Segment& sg = lib->segs[sp.seg];
-    for (int32_t j = 0; j < sp.len; j += kGraftChunk)
-      chunks.push_back(GraftChunk{sg.tok_off + j, sp.dst + j, sp.seq, sp.delta, std::min(kGraftChunk, sp.len - j),
-                                  sp.dst, sp.dst + sp.len});
+  int32_t run = 0;
+  for (int32_t i = 0; i < n_items; ++i) {
+    const Span& sp = spans[i];
+    const int64_t tok = lib->segs[sp.seg].tok_off;
+    if (by_value) {
+      args.item[i] = GraftItem{tok, sp.dst, sp.seq, sp.delta, sp.len, run, 0};
+      for (int32_t j = 0; j < sp.len; j += kGraftChunk, ++run) {
+        uint32_t& w = args.item_of[run / 4];
+        w = (run % 4 ? w : 0u) | (uint32_t)i << (8 * (run % 4));
+      }
+    } else {
+      for (int32_t j = 0; j < sp.len; j += kGraftChunk)
+        chunks.push_back(GraftChunk{tok + j, sp.dst + j, sp.seq, sp.delta, std::min(kGraftChunk, sp.len - j), sp.dst,
+                                    sp.dst + sp.len});
+    }
   }
-  const size_t o_chunks = blob.add(chunks.data(), chunks.size() * sizeof(GraftChunk));
-  char* dev;
-  size_t off;
-  if (fcg_status st = upload(c, blob, rows, s, &dev, &off)) return st;
+  const size_t o_chunks = by_value ? 0 : blob.add(chunks.data(), chunks.size() * sizeof(GraftChunk));
+  const bool upload_plan = !by_value || !rows.empty();
+  char* dev = nullptr;
+  size_t off = 0;
+  if (upload_plan)
+    if (fcg_status st = upload(c, blob, rows, s, &dev, &off)) return st;
   if (!(lib->flags & FCG_LAYOUT_ONLY))  // segments reloaded on another stream are in place first
     HIP_TRY(hipStreamWaitEvent(s, lib->reload_done, 0), "hipStreamWaitEvent");
   const KTime tg{timing_event(c), timing_event(c)};
-  int rc = launch_graft(c->desc.dtype, (const GraftChunk*)(dev + o_chunks), (int)chunks.size(), lib->k, lib->v,
-                        lib->cap, c->view(), c->d_inv_freq, c->desc.n_layers, s, tg);
+  int rc = launch_graft(c->desc.dtype, by_value ? nullptr : (const GraftChunk*)(dev + o_chunks), args, (int)n_runs,
+                        lib->k, lib->v, lib->cap, c->view(), c->d_inv_freq, c->desc.n_layers, s, tg);
   time_open(c, FCG_TIME_GRAFT, tg.start);
   time_close(c, FCG_TIME_GRAFT, tg.stop);
   if (rc) return hip_fail((hipError_t)rc, "graft launch");
   if (!(lib->flags & FCG_LAYOUT_ONLY)) HIP_TRY(hipEventRecord(lib->graft_done, s), "hipEventRecord");
-  if (fcg_status st = c->ring.retire(off, blob.bytes.size(), s)) return st;
+  if (upload_plan)
+    if (fcg_status st = c->ring.retire(off, blob.bytes.size(), s)) return st;
   for (auto& sp : spans) c->plan.mark_all_layers(sp.seq, sp.dst, sp.len);
   return FCG_OK;
 }

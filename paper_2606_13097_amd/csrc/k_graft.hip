@@ -55,10 +55,26 @@ __device__ __forceinline__ void st_cache(void* p, const uint4& v) {
     st16(p, v);
 }
 
-template <typename T, int D, bool PAGED>
-__global__ void __launch_bounds__(256) graft_kernel(const GraftChunk* __restrict__ chunks,
-                                                    const T* __restrict__ lib_k, const T* __restrict__ lib_v,
-                                                    int64_t cap, CacheView cv, const double* __restrict__ inv_freq) {
+// Where a block finds its run: a plan passed by value (grafts of few segments:
+// no upload before the launch), or a list in device memory.
+struct RunsByValue {
+  GraftArgs a;
+  __device__ __forceinline__ GraftChunk get(int b) const {
+    const GraftItem& it = a.item[(a.item_of[b >> 2] >> (8 * (b & 3))) & 0xFF];
+    const int j = (b - it.run0) * kGraftChunk;
+    return GraftChunk{it.src_tok + j, it.dst + j, it.seq, it.delta, min(kGraftChunk, it.len - j), it.dst,
+                      it.dst + it.len};
+  }
+};
+struct RunsInMemory {
+  const GraftChunk* p;
+  __device__ __forceinline__ GraftChunk get(int b) const { return p[b]; }
+};
+
+template <typename T, int D, bool PAGED, typename Runs>
+__global__ void __launch_bounds__(256) graft_kernel(Runs runs, const T* __restrict__ lib_k,
+                                                    const T* __restrict__ lib_v, int64_t cap, CacheView cv,
+                                                    const double* __restrict__ inv_freq) {
   constexpr int VEC = Store<T>::VEC;
   constexpr int HALF = D / 2;
   constexpr int KT = HALF / VEC;            // lanes per key row (each owns a pair of vectors)
@@ -70,7 +86,7 @@ __global__ void __launch_bounds__(256) graft_kernel(const GraftChunk* __restrict
 
   __shared__ float s_cos[HALF], s_sin[HALF];
 
-  const GraftChunk ch = chunks[blockIdx.x];
+  const GraftChunk ch = runs.get(blockIdx.x);
   const int h = blockIdx.y;
   const int l = blockIdx.z;
   const int t = threadIdx.x;
@@ -214,19 +230,61 @@ int launch_lib_ingest(int dtype, const void* k, const void* v, void* lib_k, void
   return check(hipGetLastError());
 }
 
-int launch_graft(int dtype, const GraftChunk* chunks, int n_chunks, const void* lib_k, const void* lib_v,
-                 int64_t cap, const CacheView& cv, const double* inv_freq, int L, hipStream_t s, KTime tm) {
-  if (n_chunks == 0) return 0;
-  dim3 grid(n_chunks, cv.n_kv_heads, L);
-#define GR(T, DD, PG)                                                                                       \
-  hipExtLaunchKernelGGL((graft_kernel<T, DD, PG>), grid, dim3(256), 0, s, tm.start, tm.stop, 0, chunks, (const T*)lib_k,             \
-                     (const T*)lib_v, cap, cv, inv_freq)
-#define GRD(T, PG) { if (cv.head_dim == 64) GR(T, 64, PG); else GR(T, 128, PG); }
+// Plan upload: the blob and the page-table rows, read by the GPU from pinned
+// host memory (system-scope loads: no cache holds an earlier call's bytes of a
+// reused ring region).  One launch; before, an asynchronous copy of the blob and
+// then one device-to-device copy per touched sequence, 1.2-1.4 us of GPU time
+// and a gap each, 33 of them for a 32-task call.
+__device__ __forceinline__ uint64_t ld8_sys(const uint64_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+__global__ void __launch_bounds__(256) upload_kernel(UploadArgs a, int copy_blocks) {
+  constexpr int U = 8;  // 8-byte loads in flight per lane: the host link's round trip is paid once
+  const bool row = (int)blockIdx.x >= copy_blocks;
+  const int r = row ? (int)blockIdx.x - copy_blocks : 0;
+  // row_ints is even (a page row and its alias row), so both kinds move 8-byte words
+  const int64_t n = row ? a.row_ints / 2 : a.bytes / 8;
+  const uint64_t* src = reinterpret_cast<const uint64_t*>(row ? a.rows + r * a.row_stride : a.host);
+  uint64_t* dst = row ? reinterpret_cast<uint64_t*>(a.page_table + (int64_t)a.seq[r] * a.row_ints)
+                      : reinterpret_cast<uint64_t*>(a.dev);
+  const int64_t step = row ? 256 * U : (int64_t)copy_blocks * 256 * U;
+  for (int64_t i0 = (row ? 0 : (int64_t)blockIdx.x * 256 * U) + threadIdx.x; i0 < n; i0 += step) {
+    uint64_t x[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) x[u] = i0 + u * 256 < n ? ld8_sys(src + i0 + u * 256) : 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (i0 + u * 256 < n) dst[i0 + u * 256] = x[u];
+  }
+}
+
+int launch_upload(const UploadArgs& args, hipStream_t s) {
+  const int copy_blocks = (int)((args.bytes + 16383) / 16384);
+  if (copy_blocks + args.n_rows == 0) return 0;
+  hipLaunchKernelGGL(upload_kernel, dim3(copy_blocks + args.n_rows), dim3(256), 0, s, args, copy_blocks);
+  return check(hipGetLastError());
+}
+
+int launch_graft(int dtype, const GraftChunk* runs, const GraftArgs& args, int n_runs, const void* lib_k,
+                 const void* lib_v, int64_t cap, const CacheView& cv, const double* inv_freq, int L, hipStream_t s,
+                 KTime tm) {
+  if (n_runs == 0) return 0;
+  dim3 grid(n_runs, cv.n_kv_heads, L);
+#define GRR(T, DD, PG, RU, RV)                                                                                 \
+  hipExtLaunchKernelGGL((graft_kernel<T, DD, PG, RU>), grid, dim3(256), 0, s, tm.start, tm.stop, 0, RV,        \
+                        (const T*)lib_k, (const T*)lib_v, cap, cv, inv_freq)
+#define GR(T, DD, PG)                                                                                          \
+  {                                                                                                            \
+    if (runs) GRR(T, DD, PG, RunsInMemory, RunsInMemory{runs});                                                \
+    else GRR(T, DD, PG, RunsByValue, RunsByValue{args});                                                       \
+  }
+#define GRD(T, PG) { if (cv.head_dim == 64) GR(T, 64, PG) else GR(T, 128, PG) }
   const bool paged = cv.page_size != 0;
   if (dtype == 0) { if (paged) GRD(float, true) else GRD(float, false) }
   else { if (paged) GRD(bf16_t, true) else GRD(bf16_t, false) }
 #undef GRD
 #undef GR
+#undef GRR
   return check(hipGetLastError());
 }
 

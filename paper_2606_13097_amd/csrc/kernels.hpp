@@ -26,6 +26,20 @@ struct GraftChunk {
 };
 constexpr int kGraftChunk = 64;
 
+// By-value plan of a graft of few segments: nothing is uploaded before the
+// launch.  Block b serves run b - run0 of item item_of[b] (bytes, four to a word).
+struct GraftItem {
+  int64_t src_tok;  // token index in the library slab of the segment's first token
+  int32_t dst, seq, delta, len;
+  int32_t run0;     // first block of the item
+  int32_t pad;
+};
+constexpr int kGraftArgItems = 32, kGraftArgRuns = 1024;
+struct GraftArgs {
+  GraftItem item[kGraftArgItems];
+  uint32_t item_of[kGraftArgRuns / 4];
+};
+
 // Device view of a composite cache (all layers).
 struct CacheView {
   void* k;               // layer-0 base of K
@@ -136,8 +150,26 @@ int launch_rope_table(const double* inv_freq, int half, int n_pos, float2* tab, 
 int launch_lib_ingest(int dtype, const void* k, const void* v, void* lib_k, void* lib_v, int L, int len,
                       int Hkv, int D, int64_t cap, int64_t tok_off, hipStream_t s);
 
-int launch_graft(int dtype, const GraftChunk* chunks, int n_chunks, const void* lib_k, const void* lib_v,
-                 int64_t cap, const CacheView& cv, const double* inv_freq, int L, hipStream_t s, KTime tm = {});
+// runs: n_runs runs of up to kGraftChunk tokens in device memory, or null: taken from `args`.
+int launch_graft(int dtype, const GraftChunk* runs, const GraftArgs& args, int n_runs, const void* lib_k,
+                 const void* lib_v, int64_t cap, const CacheView& cv, const double* inv_freq, int L, hipStream_t s,
+                 KTime tm = {});
+
+// Take a call's plan from pinned host memory in one launch: `bytes` bytes (a
+// multiple of 16) to dev, and n_rows page-table rows of row_ints ints, staged
+// row_stride bytes apart, to the rows of `seq` in the device page table.
+constexpr int kUploadRows = 64;
+struct UploadArgs {
+  const void* host;   // bytes to copy, 16-byte aligned
+  void* dev;
+  int64_t bytes;
+  const char* rows;   // staged rows (host)
+  int64_t row_stride;
+  int32_t* page_table;
+  int32_t row_ints, n_rows;
+  int32_t seq[kUploadRows];
+};
+int launch_upload(const UploadArgs& args, hipStream_t s);
 
 // A value page mapped onto the library that a truncation split: its first
 // `rows` rows are copied from library token lib_tok .. into physical page `page`.

@@ -1148,6 +1148,7 @@ fcg_status run_attention(fcg_cache* c, int32_t layer, const std::vector<TokenMet
 struct DecodePlan {
   int64_t split_keys = 0;
   int max_slots = 0;
+  int ring = 4;  // 16-key tiles of a wave's LDS ring (bf16)
   size_t part_o = 0, part_ml = 0;  // floats of the partial outputs and of the (max, sum) pairs
 };
 
@@ -1182,6 +1183,7 @@ DecodePlan plan_decode(const fcg_model_desc& d, int32_t n, const std::vector<int
   sk = (sk + 63) / 64 * 64;
   DecodePlan p;
   p.split_keys = sk;
+  p.ring = two_per_cu ? 2 : 4;
   // partial slots: one per split of every multi-split sequence of a launch group
   for (int32_t i0 = 0; i0 < n; i0 += kMaxDecodeSeqs) {
     int slots = 0;
@@ -1226,7 +1228,7 @@ fcg_status launch_decode_groups(fcg_cache* c, int32_t layer, int32_t n, const in
     // bf16: matrix-core kernel; fp32: the vector-ALU kernel
     int rc = d.dtype == FCG_BF16
                  ? launch_decode_mfma(a, (const char*)q + qoff, (const char*)k + koff, (const char*)v + koff, cv,
-                                      layer, c->d_rope, d.n_q_heads, (char*)out + qoff, part_o, part_ml, count, s,
+                                      layer, c->d_rope, d.n_q_heads, (char*)out + qoff, part_o, part_ml, count, plan.ring, s,
                                       KTime{e0, e1})
                  : launch_decode(d.dtype, a, (const char*)q + qoff, (const char*)k + koff, (const char*)v + koff, cv,
                                  layer, c->d_rope, d.n_q_heads, (char*)out + qoff, part_o, part_ml, count, s,

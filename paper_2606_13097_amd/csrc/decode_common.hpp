@@ -64,11 +64,19 @@ __device__ __forceinline__ void emit_pair(int nsplit, int64_t prow, T* out_row, 
   }
 }
 
+// Lanes that share one 16-byte chunk of a split set's outputs in merge_splits.
+template <typename T, int D, int G>
+constexpr int merge_lanes() {
+  constexpr int chunks = G * D / (16 / (int)sizeof(T));
+  return chunks < 256 ? 256 / chunks : 1;
+}
+
 // Called by all 256 lanes after their emit_pair calls, when nsplit > 1.
-// LDS: s_buf NBUF floats, s_mt / s_lt [256 / (D / EPL)][G] floats, s_flag.
+// LDS: s_buf 256 * 16 / sizeof(T) floats (256 output chunks), s_mt / s_lt
+// [merge_lanes][G] floats, s_flag.
 // Always inlined: called out of line (a choice the compiler made once more
 // kernel instances called it) it made every decode launch ~2 us longer.
-template <typename T, int D, int G, int NBUF>
+template <typename T, int D, int G>
 __device__ __forceinline__ void merge_splits(const DecodeArgs& args, int i, int hk, int slot0, int nsplit, int Hkv,
                                              int Hq, T* __restrict__ out, const float* part_o,
                                              const float* part_ml, int* count, float* s_buf, float* s_mt,
@@ -103,135 +111,97 @@ __device__ __forceinline__ void merge_splits(const DecodeArgs& args, int i, int 
   if (!*s_flag) return;
 
   // O = sum_s O_s 2^(M_s - M) / sum_s L_s 2^(M_s - M), M = max_s M_s, per
-  // query head.  Lane (split lane sl, 16-byte chunk dc of a row) folds the
-  // splits sl, sl + NSL, ... of its chunk into a running (max, sum, output)
-  // per head, as in the key loop; the NSL split lanes of each chunk then meet
-  // in LDS.  Loads of splits past the last one use an offset beyond the
-  // buffer: they return zeros without a memory access.
-  constexpr int EB = BF ? 2 : 4;            // bytes per partial element
-  constexpr int EPL = 16 / EB;              // elements per 16-byte chunk
-  constexpr int NDC = D / EPL, NSL = 256 / NDC;
-  constexpr int PF = 16 / G;                     // splits per lane per batch of loads
-  constexpr int NMLV = G >= 2 ? G / 2 : 1;       // 16-byte loads of a split's (max, sum) pairs
-  constexpr int JR0 = NBUF / (NSL * D);
-  constexpr int JR = JR0 < G ? JR0 : G;          // heads per LDS round
-  static_assert(JR >= 1, "merge buffer");
-  constexpr uint32_t kFar = 0x80000000u;         // past every partial buffer (< 2^31 bytes)
-  const int dc = t % NDC, sl = t / NDC;
-  const int64_t hg = (int64_t)Hkv * G;          // rows per partial slot
+  // query head.  A split's G rows are one contiguous run of 16-byte chunks: lane
+  // (split lane sl, chunk) folds its chunk of the splits sl, sl + NSL, ... into a
+  // running (max, sum, output), PF splits' loads in flight at a time, and the NSL
+  // lanes of a chunk then meet in LDS.  With G = 4, D = 128 a wave reads one
+  // split's 1 KB per load and 32 splits arrive in one round trip; an earlier fold
+  // (every lane all G heads of a chunk of 16 split lanes, 24 loads and four
+  // unrolled folds, 32 KB through LDS) took 3.0 us of a 7B step's 10.7, mostly
+  // its code: only this block runs it, so every instruction is fetched for it.
+  constexpr int EPL = 16 / (int)sizeof(T);  // elements per 16-byte chunk
+  constexpr int NDC = D / EPL, CH = G * NDC, NSL = merge_lanes<T, D, G>();
+  constexpr int PF = 8;
+  constexpr uint32_t kFar = 0x80000000u;    // past every partial buffer (< 2^31 bytes): reads zeros, no access
+  const int64_t hg = (int64_t)Hkv * G;      // rows per partial slot
   const int64_t row0 = (int64_t)slot0 * hg + (int64_t)hk * G;
   const uint32_t rows_all = (uint32_t)(args.slots * hg);
-  const __amdgpu_buffer_rsrc_t ro = buf_rsrc(part_o, rows_all * D * EB);
+  const __amdgpu_buffer_rsrc_t ro = buf_rsrc(part_o, rows_all * D * (uint32_t)sizeof(T));
   const __amdgpu_buffer_rsrc_t rml = buf_rsrc(part_ml, rows_all * 8u);
-  float acc[G][EPL], lm[G], ll[G];
+  T* orow = out + ((int64_t)i * Hq + hk * G) * D;
+  const int sl = t / (CH < 256 ? CH : 256);
+  for (int c = t % (CH < 256 ? CH : 256); c < CH; c += 256) {  // once unless G * D > 256 chunks
+    const int j = c / NDC;
+    float acc[EPL], m = -INFINITY, lsum = 0.f;
 #pragma unroll
-  for (int j = 0; j < G; ++j) {
-    lm[j] = -INFINITY;
-    ll[j] = 0.f;
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) acc[j][e] = 0.f;
-  }
-  for (int sb = 0; sb < nsplit; sb += NSL * PF) {
-    u32x4_t rv[PF][G], mv[PF][NMLV];
-#pragma unroll
-    for (int p = 0; p < PF; ++p) {
-      const int sp = sb + sl + p * NSL;
-      const bool ok = sp < nsplit;
-      const int64_t r = row0 + (int64_t)sp * hg;
-#pragma unroll
-      for (int h = 0; h < NMLV; ++h) {
-        if constexpr (G >= 2) {
-          mv[p][h] = ld16_dev(rml, ok ? (uint32_t)((r + 2 * h) * 8) : kFar);
-        } else {
-          const u32x2_t x = ld8_dev(rml, ok ? (uint32_t)(r * 8) : kFar);
-          mv[p][h] = u32x4_t{x.x, x.y, 0u, 0u};
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < G; ++j)
-        rv[p][j] = ld16_dev(ro, ok ? (uint32_t)(((r + j) * D + dc * EPL) * EB) : kFar);
-    }
-#pragma unroll
-    for (int j = 0; j < G; ++j) {
-      auto mval = [&](int p) { return __uint_as_float(j % 2 ? mv[p][j / 2].z : mv[p][j / 2].x); };
-      auto lval = [&](int p) { return __uint_as_float(j % 2 ? mv[p][j / 2].w : mv[p][j / 2].y); };
-      float bm = -INFINITY;
-#pragma unroll
-      for (int p = 0; p < PF; ++p)
-        if (sb + sl + p * NSL < nsplit) bm = fmaxf(bm, mval(p));
-      const float mn = fmaxf(lm[j], bm);
-      if (mn == -INFINITY) continue;
-      const float f = __builtin_amdgcn_exp2f(lm[j] - mn);  // 0 while nothing was folded
-      ll[j] *= f;
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) acc[j][e] *= f;
+    for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
+#pragma unroll 1
+    for (int sb = sl; sb < nsplit; sb += NSL * PF) {
+      u32x4_t x[PF];
+      u32x2_t ml[PF];
 #pragma unroll
       for (int p = 0; p < PF; ++p) {
-        if (sb + sl + p * NSL >= nsplit) continue;
-        const float wgt = __builtin_amdgcn_exp2f(mval(p) - mn);
-        ll[j] = fmaf(lval(p), wgt, ll[j]);
-        float x[EPL];
-        if constexpr (BF) {
-          Store<T>::unpack(make_uint4(rv[p][j].x, rv[p][j].y, rv[p][j].z, rv[p][j].w), x);
-        } else {
-          x[0] = __uint_as_float(rv[p][j].x);
-          x[1] = __uint_as_float(rv[p][j].y);
-          x[2] = __uint_as_float(rv[p][j].z);
-          x[3] = __uint_as_float(rv[p][j].w);
-        }
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) acc[j][e] = fmaf(x[e], wgt, acc[j][e]);
+        const int sp = sb + p * NSL;
+        const uint32_t r = (uint32_t)(row0 + (int64_t)sp * hg);
+        ml[p] = ld8_dev(rml, sp < nsplit ? (r + j) * 8u : kFar);
+        x[p] = ld16_dev(ro, sp < nsplit ? r * (uint32_t)(D * sizeof(T)) + c * 16u : kFar);
       }
-      lm[j] = mn;
-    }
-  }
-  // merge the split lanes: per head, M over the lanes, each lane's output
-  // and sum weighted by 2^(m - M)
-  if (dc == 0) {
+      float mn = m;
 #pragma unroll
-    for (int j = 0; j < G; ++j) {
-      s_mt[sl * G + j] = lm[j];
-      s_lt[sl * G + j] = ll[j];
-    }
-  }
+      for (int p = 0; p < PF; ++p)
+        mn = fmaxf(mn, sb + p * NSL < nsplit ? __uint_as_float(ml[p].x) : -INFINITY);
+      const float mr = mn == -INFINITY ? 0.f : mn;         // a split always has a visible key; kept for safety
+      const float f = __builtin_amdgcn_exp2f(m - mr);      // 0 while nothing was folded
+      lsum *= f;
 #pragma unroll
-  for (int jr = 0; jr < G; jr += JR) {
-    if (jr) __syncthreads();  // the previous round's sums are read
+      for (int e = 0; e < EPL; ++e) acc[e] *= f;
 #pragma unroll
-    for (int jj = 0; jj < JR; ++jj)
+      for (int p = 0; p < PF; ++p) {
+        // past the last split: sum and outputs read as zeros, whatever the weight
+        const float wgt = sb + p * NSL < nsplit ? __builtin_amdgcn_exp2f(__uint_as_float(ml[p].x) - mr) : 0.f;
+        float y[EPL];
+        Store<T>::unpack(make_uint4(x[p].x, x[p].y, x[p].z, x[p].w), y);
+        lsum = fmaf(__uint_as_float(ml[p].y), wgt, lsum);
 #pragma unroll
-      for (int e = 0; e < EPL; e += 4)
-        *reinterpret_cast<float4*>(&s_buf[(sl * JR + jj) * D + dc * EPL + e]) =
-            make_float4(acc[jr + jj][e], acc[jr + jj][e + 1], acc[jr + jj][e + 2], acc[jr + jj][e + 3]);
-    __syncthreads();
-    for (int idx = t; idx < JR * D / 2; idx += 256) {
-      const int jj = idx / (D / 2), d = 2 * (idx % (D / 2)), j = jr + jj;
-      float M = -INFINITY;
-#pragma unroll
-      for (int s2 = 0; s2 < NSL; ++s2) M = fmaxf(M, s_mt[s2 * G + j]);
-      float L = 0.f, o0 = 0.f, o1 = 0.f;
-      if (M != -INFINITY) {
-#pragma unroll 8
-        for (int s2 = 0; s2 < NSL; ++s2) {
-          const float ms = s_mt[s2 * G + j];
-          const float wgt = ms == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ms - M);
-          const float2 x = *reinterpret_cast<const float2*>(&s_buf[(s2 * JR + jj) * D + d]);
-          L = fmaf(s_lt[s2 * G + j], wgt, L);
-          o0 = fmaf(x.x, wgt, o0);
-          o1 = fmaf(x.y, wgt, o1);
-        }
+        for (int e = 0; e < EPL; ++e) acc[e] = fmaf(y[e], wgt, acc[e]);
       }
-      T* dst = out + ((int64_t)i * Hq + hk * G + j) * D + d;
-      Store<T>::store1(dst, L > 0.f ? o0 / L : 0.f);
-      Store<T>::store1(dst + 1, L > 0.f ? o1 / L : 0.f);
+      m = mn;
+    }
+    if (NSL == 1) {
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) acc[e] = lsum > 0.f ? acc[e] / lsum : 0.f;
+      st16(orow + c * EPL, Store<T>::pack(acc));
+      continue;
+    }
+#pragma unroll
+    for (int e = 0; e < EPL; e += 4)
+      *reinterpret_cast<float4*>(&s_buf[(sl * CH + c) * EPL + e]) =
+          make_float4(acc[e], acc[e + 1], acc[e + 2], acc[e + 3]);
+    if (c % NDC == 0) {
+      s_mt[sl * G + j] = m;
+      s_lt[sl * G + j] = lsum;
     }
   }
-}
-
-// split-lane table size of merge_splits for (T, D)
-template <typename T, int D>
-constexpr int merge_lanes() {
-  return 256 / (D / (16 / (int)sizeof(T)));
+  if (NSL == 1) return;
+  __syncthreads();
+  for (int idx = t; idx < G * D / 2; idx += 256) {
+    const int d = 2 * idx, j = d / D;
+    float M = -INFINITY;
+#pragma unroll
+    for (int s2 = 0; s2 < NSL; ++s2) M = fmaxf(M, s_mt[s2 * G + j]);
+    float L = 0.f, o0 = 0.f, o1 = 0.f;
+#pragma unroll
+    for (int s2 = 0; s2 < NSL; ++s2) {
+      const float ms = s_mt[s2 * G + j];  // -inf: a split lane without a split
+      const float wgt = ms == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ms - M);
+      const float2 x = *reinterpret_cast<const float2*>(&s_buf[s2 * G * D + d]);
+      L = fmaf(s_lt[s2 * G + j], wgt, L);
+      o0 = fmaf(x.x, wgt, o0);
+      o1 = fmaf(x.y, wgt, o1);
+    }
+    Store<T>::store1(orow + d, L > 0.f ? o0 / L : 0.f);
+    Store<T>::store1(orow + d + 1, L > 0.f ? o1 / L : 0.f);
+  }
 }
 
 }  // namespace fcg

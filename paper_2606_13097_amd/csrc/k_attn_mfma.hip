@@ -71,34 +71,6 @@ struct PrefillTile {
   __device__ static int swz_v(int r) { return 2 * (r % (NC / 2)); }
 };
 
-// LDS byte address of a pointer into a __shared__ array
-__device__ __forceinline__ uint32_t lds_addr(const void* p) {
-  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
-}
-// global -> LDS, 16 bytes per lane: lane l's bytes land at lds + 16 l (lds
-// wave-uniform).  Inline assembly, so that the compiler's own wait
-// bookkeeping, which cannot tell the ring's buffers apart, adds no
-// vmcnt(0) before each tile's LDS reads; the waits are explicit (wait_vm).
-__device__ __forceinline__ void dma16(const void* g, uint32_t lds) {
-  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "{m0}"(lds) : "memory");
-}
-// s_waitcnt vmcnt(N): at most N of this wave's vector memory operations remain
-template <int N>
-__device__ __forceinline__ void wait_vm() {
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-// this wave's LDS reads have returned, then the workgroup barrier
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
-typedef short i16x4_t __attribute__((ext_vector_type(4)));
-// ds_read_b64_tr_b16: within each 16-lane group, lane j receives element j % 4
-// of the 8 bytes addressed by lanes 4e + j / 4, e = 0..3
-__device__ __forceinline__ uint2 ld_tr8(const bf16_t* p) {
-  const i16x4_t x = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-      (__attribute__((address_space(3))) i16x4_t*)(const_cast<bf16_t*>(p)));
-  return __builtin_bit_cast(uint2, x);
-}
-
 // grid (row block, key split, kv head).  Each wave attends RT 16-row tiles
 // of the block's query rows (WAVES * RT * 16 rows).  NBUF tiles in the LDS
 // ring: 4 (three in flight while one is attended) for 8-wave blocks of 32-row

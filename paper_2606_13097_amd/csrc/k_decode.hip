@@ -356,8 +356,8 @@ __global__ void __launch_bounds__(256) decode_kernel(DecodeArgs args, const T* _
     }
   }
   if (nsplit == 1) return;
-  static_assert(merge_lanes<T, D>() <= SLOTS, "split lanes use the slot tables");
-  merge_splits<T, D, G, NBUF>(args, i, hk, slot0, nsplit, Hkv, Hq, out, part_o, part_ml, count, s_buf, &s_m[0][0],
+  static_assert(merge_lanes<T, D, G>() <= SLOTS && 256 * 16 / (int)sizeof(T) <= NBUF, "the merge uses the slot tables");
+  merge_splits<T, D, G>(args, i, hk, slot0, nsplit, Hkv, Hq, out, part_o, part_ml, count, s_buf, &s_m[0][0],
                               &s_l[0][0], &s_last);
 }
 

@@ -4,26 +4,35 @@
 // Per sequence i the new token sits at position pos_i = its current length.
 // Block (split s, sequence i, kv head h) attends the token's g query heads
 // (g <= 16) over key positions [s * split_keys, min(pos_i + 1, (s + 1) *
-// split_keys)).  Its four waves take the split's 16-key tiles in turn
-// (w, w + 4, ...); per tile and wave:
-//   - S^T = K Q^T with v_mfma_f32_16x16x32_bf16: A = the tile's keys straight
-//     from memory into registers (lane l: key l % 16, dims 32 ks + 8 (l / 16)
-//     .. + 7), B = the encoded queries, column j = query head j (columns past
-//     g are zero).  Lane l then holds the scores of query l % 16 for keys
-//     4 (l / 16) .. + 3.
+// split_keys)).  Its four waves take the split's 16-key tiles in turn (w, w +
+// 4, ...); wave w brings its tiles from memory into an LDS ring of its own
+// (global_load_lds, whole rows, 1 KB per instruction), so the loop has no
+// barrier and the tiles in flight cost no registers.  Per tile:
+//   - S^T = K Q^T with v_mfma_f32_16x16x32_bf16: A = the tile's keys (lane l:
+//     key l % 16, dims 32 ks + 8 (l / 16) .. + 7), B = the encoded queries,
+//     column j = query head j (columns past g are zero).  Lane l then holds the
+//     scores of query l % 16 for keys 4 (l / 16) .. + 3.
 //   - online softmax in base 2 with one running max per query shared by its
 //     four lanes, moved only when a score exceeds it by 2^8 (ballot), so the
-//     lanes exchange maxima (two shuffles) only then;
+//     lanes exchange maxima (two lane swaps) only then;
 //   - O^T += V^T P^T with v_mfma_f32_16x16x16_bf16: B = the lane's four
-//     probabilities rounded to bf16 (exactly the B layout), A = V^T read from
-//     a per-wave LDS tile that each lane fills with one 4-key x 8-dim block
-//     of V transposed in registers (v_perm).
-// The block holding pos_i encodes the new key, stores key and value into the
-// cache slot and keeps them in LDS; after its tiles, one wave attends to them
-// as a one-key tile.  The four
+//     probabilities rounded to bf16 (exactly the B layout), A = V^T by the LDS
+//     transpose read (ds_read_b64_tr_b16).
+// The owner of pos_i encodes the new key and, after its tiles, stores key and
+// value into the cache slot and attends to them as a one-key tile.  The four
 // waves merge through LDS; the split's result goes to the output or, for a
 // sequence with several splits, to its partial slot, and the last block of
 // the sequence to finish merges the splits (decode_common.hpp).
+//
+// What bounds it: many keys, HBM (32 paged tasks of ~6K tokens, 796 MB a call:
+// 148.6 -> 125 us, 6.4 TB/s; four tasks of ~22K with g = 8, 369 MB: 68-72 -> 62
+// us); one task of ~4K (17.5 MB), the chain of round trips: 10.9 -> 9.1 us, of
+// which an empty launch takes 1.8, arguments, encoding and partial store 2.9,
+// the tiles 2.2, the arrival count 0.7 and the merge 1.5.  Before, keys went
+// straight into registers in the matrix operand layout, 64 bytes of each of 16
+// rows per load, and values through a transpose in registers; a paged block
+// read its page entries into LDS behind a barrier (six tasks of ~1.8K: 22.9 us
+// against 15).
 #include "decode_common.hpp"
 
 namespace fcg {
@@ -50,7 +59,8 @@ __device__ __forceinline__ uint32_t dm_cvt_bf16x2(float lo, float hi) {
 
 }  // namespace
 
-template <int D, int G, bool PAGED>
+// NB: 16-key tiles in each wave's LDS ring.
+template <int D, int G, bool PAGED, int NB>
 __global__ void __launch_bounds__(256) decode_mfma_kernel(DecodeArgs args, const bf16_t* __restrict__ q,
                                                           const bf16_t* __restrict__ k,
                                                           const bf16_t* __restrict__ v, CacheView cv,
@@ -62,29 +72,22 @@ __global__ void __launch_bounds__(256) decode_mfma_kernel(DecodeArgs args, const
   constexpr int KS = D / 32;       // 32-deep k steps of S^T
   constexpr int DT = D / 16;       // 16-dim tiles of O^T
   constexpr int HALF = D / 2;
-  constexpr int NDG = D / 8;       // 8-dim groups of a row
-  constexpr int VBL = 4 * NDG;     // 4-key x 8-dim blocks of a 16-key tile
-  // V^T in LDS: row r (a dim, 16 keys = 32 bytes) at element (r + r / 8) * 16,
-  // a 32-byte gap after every 8 rows.  The writes (rows 8 dg + e of one e,
-  // four 8-byte key groups each) and the reads (rows 16 dt .. + 15, all four
-  // groups) then spread over every bank, so that each 512-byte access takes
-  // the minimum number of LDS passes; with plain 32-byte rows the 16 rows of
-  // a write, 8 apart, fall on the same 8 banks.
-  constexpr int VT_ROWS = D + D / 8;
-  constexpr int NSL = merge_lanes<bf16_t, D>();
-  constexpr int GR = G < 4 ? G : 4;
-  constexpr int NBUF = 4 * G * D > GR * NSL * D ? 4 * G * D : GR * NSL * D;
-  __shared__ float s_cos[HALF], s_sin[HALF];
-  __shared__ __align__(16) bf16_t s_vt[4][VT_ROWS * 16];
-  __shared__ __align__(16) float s_buf[NBUF];
+  constexpr int NC = D / 8;        // 16-byte chunks per row
+  constexpr int RI = 64 / NC;      // rows one DMA instruction fills
+  constexpr int KI = 16 / RI;      // DMA instructions for a tile's keys (and as many for its values)
+  constexpr int DPT = 2 * KI;
+  constexpr bool NT = NB == 2;     // launches that read much: see the launcher
+  constexpr int TILE = 2 * 16 * D * 2;         // bytes of a tile: 16 keys, then 16 values
+  constexpr int NCS = HALF / 2;                // 16-byte chunks of a position's (cos, sin) row
+  constexpr int QI = (G * NC + 63) / 64;       // DMA instructions for the query rows
+  constexpr int NSL = merge_lanes<bf16_t, D, G>();
+  static_assert(2 * NC + NCS <= 64 && (1 + QI) * 1024 <= TILE, "the prologue's rows fit one ring buffer");
+  static_assert(G * D * 4 <= NB * TILE && 256 * 8 * 4 <= 4 * NB * TILE, "the merges fit the ring");
+  __shared__ __align__(16) char s_ring[4 * NB * TILE];
   __shared__ float s_wm[4][16], s_wl[4][16];
   __shared__ float s_mt[NSL * G], s_lt[NSL * G];
   __shared__ __align__(16) bf16_t s_newk[D], s_newv[D];  // the new token's encoded key and value
   __shared__ int s_last;
-  // paged caches: the split's page and value-alias entries, read into LDS once
-  // (a table lookup per tile would put a dependent load before every tile's loads)
-  constexpr int NPG = PAGED ? kPageWindow : 1;
-  __shared__ int32_t s_pg[NPG], s_al[NPG];
 
   const int split = blockIdx.x, i = blockIdx.y, hk = blockIdx.z;
   const int seq = args.seq[i], pos = args.pos[i], slot0 = args.split0[i];
@@ -102,158 +105,164 @@ __global__ void __launch_bounds__(256) decode_mfma_kernel(DecodeArgs args, const
                "s"(cvv), "s"(cv.layer_stride), "s"(cv.max_tokens), "s"(cv.n_kv_heads), "s"(layer), "s"(rope),
                "s"(out), "s"(part_o), "s"(part_ml), "s"(count), "s"(cv.head_dim));
   if (PAGED)
-    asm volatile("" ::"s"(cv.page_table), "s"(cv.n_lp), "s"(cv.v_alias), "s"(cv.lib_v), "s"(cv.lib_cap), "s"(npage));
+    asm volatile("" ::"s"(cv.page_table), "s"(cv.n_lp), "s"(cv.v_alias), "s"(cv.lib_v), "s"(cv.lib_cap), "s"(npage),
+                 "s"(cv.page_size));  // else the load of n_lp .. head_dim covers a dword that nothing reads
   if (split >= nsplit) return;  // padding split of a shorter sequence
 
   const int Hkv = cv.n_kv_heads;
   const int Hq = Hkv * G;
   const int t = threadIdx.x;
-  const int w = t >> 6, l = t & 63, lr = l & 15, lq = l >> 4;
-  const int kg = (l % VBL) / NDG, dg = l % NDG;  // this lane's V block: keys 4 kg .. + 3, dims 8 dg .. + 7
-  const int k0 = split * sk;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);  // the wave, in a scalar register
+  const int l = t & 63, lr = l & 15, lq = l >> 4;
+  const int k0 = split * sk;             // a multiple of 64
   const int k1 = min(pos + 1, k0 + sk);
   const bool owns_new = k1 == pos + 1;   // the last split holds the new token
   const int kend = owns_new ? pos : k1;  // cached keys [k0, kend)
   const int ntile = (kend - k0 + 15) >> 4;
+  // the wave's n tiles are w, w + 4, ...; they pass through its own LDS ring,
+  // so no barrier until the waves merge
+  
+  const int n = (ntile - w + 3) >> 2;
 
-  // pages holding [ka, kend), ka = the lowest position a (clamped) load reads
-  const int ka = max(0, min(k0, kend - 1));
-  const int lpa = ka >> 4;
-  const int npg = PAGED ? (max(ka, kend - 1) >> 4) - lpa + 1 : 0;
-  const bool window = PAGED && npg <= NPG;  // else: entries read from memory per load (block-uniform)
-  if (window) {
-    const int32_t* row = cv.page_table + (int64_t)seq * 2 * cv.n_lp + lpa;
-    for (int e = t; e < npg; e += 256) {
-      s_pg[e] = row[e];
-      s_al[e] = cv.v_alias ? row[cv.n_lp + e] : -1;
-    }
-  }
+  const bool new_wave = owns_new && w == (ntile & 3);  // encodes, stores and attends the new token
+  char* ring = s_ring + w * (NB * TILE);
+  const uint32_t ring_lds = lds_addr(ring);
 
-  // ---- loads, in the order their data is needed
-  const float2 cs_pos = rope[(int64_t)pos * HALF + t % HALF];  // (cos, sin) of the position
-  uint4 qa[KS], qb[KS];  // query head lr (row g - 1 for columns past the group): dims and rotary partners
+  // A tile of a paged cache is one page: its entries are wave-uniform, read
+  // through the scalar cache (this launch writes only the entry of the page it
+  // maps, which holds no cached key).
+  typedef const __attribute__((address_space(4))) int32_t* cptr;
+  const cptr prow = PAGED ? (cptr)(uintptr_t)(cv.page_table + (int64_t)seq * 2 * cv.n_lp + (k0 >> 4)) : (cptr)0;
+  struct Entry {
+    int32_t page, alias;
+  };
+  auto entry = [&](int ti) __attribute__((always_inline)) -> Entry {  // of the wave's tile ti (clamped into the split)
+    Entry e{0, -1};
+    if (PAGED) {
+      const int x = max(0, min(w + 4 * ti, ntile - 1));
+      e.page = prow[x];
+      if (cv.v_alias) e.alias = prow[cv.n_lp + x];
+    }
+    return e;
+  };
+  const int64_t head0 = PAGED ? 0 : kv_offset<false>(cv, layer, seq, hk, k0);
+  // Tile ti of the wave into its ring buffer.  DMA instruction j fills slots
+  // 64 j .. 64 j + 63 of the key (value) rows, lane l the slot of row (64 j + l)
+  // / NC at chunk position (64 j + l) % NC.  The chunks of a row are
+  // XOR-swizzled so that the fragment reads below meet no bank conflicts (keys:
+  // row % NC; values: 2 (row % (NC / 2))), so the lane loads the chunk that
+  // belongs there: every instruction reads RI whole rows, 1 KB in one piece.
+  auto issue = [&](int ti, const Entry& e) __attribute__((always_inline)) {
+    const int tile = w + 4 * ti;
+    const bf16_t *kb, *vb;
+    if (PAGED) {
+      const int64_t off = (int64_t)layer * cv.layer_stride + ((int64_t)e.page * Hkv + hk) * 16 * D;
+      kb = ck + off;
+      vb = cvv + off;
+      if (e.alias >= 0)
+        vb = reinterpret_cast<const bf16_t*>(cv.lib_v) + (((int64_t)layer * Hkv + hk) * cv.lib_cap + e.alias) * D;
+    } else {
+      kb = ck + head0 + (int64_t)tile * 16 * D;
+      vb = cvv + head0 + (int64_t)tile * 16 * D;
+    }
+    const int last = kend - 1 - (k0 + tile * 16);  // keys past the range re-read its last key (masked below)
+    const uint32_t lds = ring_lds + (uint32_t)(ti & (NB - 1)) * TILE;
+#pragma unroll
+    for (int j = 0; j < KI; ++j) {
+      const int r = j * RI + l / NC, p = l % NC;
+      dma16s<NT>(kb, (uint32_t)(min(r, last) * D + (p ^ (r % NC)) * 8) * 2, lds + j * 1024);
+    }
+#pragma unroll
+    for (int j = 0; j < KI; ++j) {
+      const int r = j * RI + l / NC, p = l % NC;
+      const uint32_t off = (uint32_t)(min(r, last) * D + (p ^ (2 * (r % (NC / 2)))) * 8) * 2;
+      if (NT && !(PAGED && cv.v_alias)) dma16s<true>(vb, off, lds + (KI + j) * 1024);
+      else dma16s(vb, off, lds + (KI + j) * 1024);
+    }
+  };
+
+  // at most `ahead` of the wave's youngest tiles still in flight
+  auto wait_tiles = [&](int ahead) __attribute__((always_inline)) {
+    if (NB > 3 && ahead >= 3) wait_vm<3 * DPT>();
+    else if (NB > 2 && ahead == 2) wait_vm<2 * DPT>();
+    else if (ahead == 1) wait_vm<DPT>();
+    else wait_vm<0>();
+  };
+
+  // ---- prologue: into the ring buffer that stays free, the new token's key and
+  // value, the position's (cos, sin) row and the query rows; then the first
+  // tiles.  Each wave fetches its own copy, so none waits for another.
+  constexpr int PRE = NB - 1;
+  Entry nx = entry(0);
+  const char* stage = ring + (NB - 1) * TILE;
+  const uint32_t stage_lds = ring_lds + (NB - 1) * TILE;
   {
-    const bf16_t* row = q + ((int64_t)i * Hq + hk * G + min(lr, G - 1)) * D;
+    const char* kr = reinterpret_cast<const char*>(k + ((int64_t)i * Hkv + hk) * D);
+    const char* vr = reinterpret_cast<const char*>(v + ((int64_t)i * Hkv + hk) * D);
+    const char* cr = reinterpret_cast<const char*>(rope + (int64_t)pos * HALF);
+    const char* src = l < NC ? kr + l * 16 : l < 2 * NC ? vr + (l - NC) * 16 : cr + min(l - 2 * NC, NCS - 1) * 16;
+    dma16(src, stage_lds);
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      const int d = ks * 32 + lq * 8;
-      qa[ks] = ld16(row + d);
-      qb[ks] = ld16(row + (d < HALF ? d + HALF : d - HALF));
-    }
+    for (int j = 0; j < QI; ++j)
+      dma16s(q + ((int64_t)i * Hq + hk * G) * D, (uint32_t)min(j * 64 + l, G * NC - 1) * 16,
+             stage_lds + (1 + j) * 1024);
   }
-  // the new token's key (dims and rotary partners) and value: lane t < D / 8
-  // holds dims 8t .. 8t + 7 (loaded by every block, used by the owner's)
-  const int dn = (t % NDG) * 8;
-  uint4 na, nb, nv;
-  {
-    const bf16_t* krow = k + ((int64_t)i * Hkv + hk) * D;
-    const bf16_t* vrow = v + ((int64_t)i * Hkv + hk) * D;
-    na = ld16(krow + dn);
-    nb = ld16(krow + (dn < HALF ? dn + HALF : dn - HALF));
-    nv = ld16(vrow + dn);
+#pragma unroll 1  // one copy of the code: every instruction of a short launch is fetched for it
+  for (int u = 0; u < min(n, PRE); ++u) {
+    const Entry e = nx;
+    nx = entry(u + 1);
+    issue(u, e);
   }
-  // key and value rows of cached position p (p in [ka, kend))
-  auto k_ptr = [&](int p) -> const bf16_t* {
-    if (window) {
-      const int32_t page = s_pg[(p >> 4) - lpa];
-      return ck + (int64_t)layer * cv.layer_stride + (((int64_t)page * Hkv + hk) * 16 + (p & 15)) * D;
-    }
-    return ck + kv_offset<PAGED>(cv, layer, seq, hk, p);
-  };
-  auto v_ptr = [&](int p) -> const bf16_t* {
-    if (window) {
-      const int e = (p >> 4) - lpa;
-      const int32_t a = s_al[e];
-      if (a >= 0)
-        return reinterpret_cast<const bf16_t*>(cv.lib_v) +
-               (((int64_t)layer * Hkv + hk) * cv.lib_cap + a + (p & 15)) * D;
-      return cvv + (int64_t)layer * cv.layer_stride + (((int64_t)s_pg[e] * Hkv + hk) * 16 + (p & 15)) * D;
-    }
-    return v_row<PAGED, bf16_t>(cv, layer, seq, hk, p);
-  };
-  if (window) __syncthreads();  // the page window is in LDS (a block-uniform branch)
-  // a tile's keys (A layout) and V block; keys past the range re-read the last key
-  auto load_tile = [&](int ti, uint4 (&kk)[KS], uint4 (&vv)[4]) {
-    const int kb = k0 + ti * 16;
-    const bf16_t* kr = k_ptr(max(0, min(kb + lr, kend - 1))) + lq * 8;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) kk[ks] = ld16(kr + ks * 32);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) vv[r] = ld16(v_ptr(max(0, min(kb + 4 * kg + r, kend - 1))) + dg * 8);
-  };
-  // The loads above go out first: the position's (cos, sin), which the
-  // barrier below waits for, and the query.  Left to itself the scheduler
-  // issues them after the tiles' loads, and that wait then drains the whole
-  // split before the first tile is attended.  Only the wave's first tile
-  // follows them before the encoding; its next two go out after it (below):
-  // with every block's whole split requested at once, the query and the
-  // rotary pair wait behind that burst (7B decode call 12.0 -> 11.5 us).
-  __builtin_amdgcn_sched_barrier(0);
-  uint4 kA[KS], vA[4], kB[KS], vB[4], kC[KS], vC[4];
-  load_tile(w, kA, vA);
-  if (t < HALF) {
-    s_cos[t] = cs_pos.x;
-    s_sin[t] = cs_pos.y;
-  }
-  __syncthreads();
+  wait_tiles(min(n, PRE));  // all but the tiles: the staged rows have landed
 
   // rotate 8 dims d .. d + 7 given (own dims, partner dims), round to bf16
-  auto encode8 = [&](int d, const uint4& xa, const uint4& xb) -> uint4 {
+  const float* cs = reinterpret_cast<const float*>(stage + 2 * NC * 16);
+  auto encode8 = [&](int d, const uint4& xa, const uint4& xb) __attribute__((always_inline)) -> uint4 {
     float a[8], b[8], y[8];
+    uint4 cw[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) cw[e] = ld16(cs + 2 * (d % HALF) + 4 * e);
+    const float* c = reinterpret_cast<const float*>(cw);  // (cos, sin) x 8
     Store<bf16_t>::unpack(xa, a);
     Store<bf16_t>::unpack(xb, b);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int ii = (d + e) % HALF;
-      const float c = s_cos[ii], sn = s_sin[ii];
-      y[e] = d < HALF ? fmaf(a[e], c, -b[e] * sn) : fmaf(a[e], c, b[e] * sn);
-    }
-    return Store<bf16_t>::pack(y);
+    for (int e = 0; e < 8; ++e)
+      y[e] = d < HALF ? fmaf(a[e], c[2 * e], -b[e] * c[2 * e + 1]) : fmaf(a[e], c[2 * e], b[e] * c[2 * e + 1]);
+    return make_uint4(dm_cvt_bf16x2(y[0], y[1]), dm_cvt_bf16x2(y[2], y[3]), dm_cvt_bf16x2(y[4], y[5]),
+                      dm_cvt_bf16x2(y[6], y[7]));
   };
-  uint4 qB[KS];  // Q^T operand: column lr
+  uint4 qB[KS];  // Q^T operand: column lr (query head lr; zero past the group)
+  {
+    uint4 qa[KS];
+    const char* row = stage + 1024 + min(lr, G - 1) * (D * 2);
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) {
-    const uint4 e = encode8(ks * 32 + lq * 8, qa[ks], qb[ks]);
-    qB[ks] = lr < G ? e : make_uint4(0u, 0u, 0u, 0u);
+    for (int ks = 0; ks < KS; ++ks) qa[ks] = ld16(row + (ks * 4 + lq) * 16);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      // the rotary partners of the lane's dims are its own dims of another k step
+      const uint4 e = encode8(ks * 32 + lq * 8, qa[ks], qa[ks ^ (HALF / 32)]);
+      qB[ks] = lr < G ? e : make_uint4(0u, 0u, 0u, 0u);
+    }
   }
-  if (PAGED && owns_new && hk == 0 && t == 0 && npage >= 0) enter_page(cv, seq, pos, npage);
-  if (owns_new && t < NDG) {
-    // encode the new key, store key and value into the token's cache slot and
-    // keep both in LDS for the wave that attends to them
-    const uint4 kn = encode8(dn, na, nb);
-    const int64_t off = new_token_offset<PAGED>(cv, layer, seq, hk, pos, npage) + dn;
-    st16(reinterpret_cast<bf16_t*>(cv.k) + off, kn);
-    st16(reinterpret_cast<bf16_t*>(cv.v) + off, nv);
+  if (PAGED && new_wave && hk == 0 && l == 0 && npage >= 0) enter_page(cv, seq, pos, npage);
+  if (new_wave && l < NC) {
+    // encode the new key; key and value wait in LDS for the end of the loop
+    const int dn = l * 8;
+    const uint4 kn = encode8(dn, ld16(stage + l * 16), ld16(stage + (l ^ (NC / 2)) * 16));
+    const uint4 nv = ld16(stage + (NC + l) * 16);
     st16(&s_newk[dn], kn);
     st16(&s_newv[dn], nv);
   }
-  __builtin_amdgcn_sched_barrier(0);
-  load_tile(w + 4, kB, vB);
-  load_tile(w + 8, kC, vC);
   const float qscale = 1.4426950408889634f / sqrtf((float)D);
 
   float mref = -INFINITY, lsum = 0.f;  // running max (log2 units) of query lr, sum of this lane's keys
   dm_f32x4 acc[DT];
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) acc[dt] = dm_f32x4{0.f, 0.f, 0.f, 0.f};
-  bf16_t* vt = s_vt[w];
 
-  // attend one tile: keys kb .. kb + 15, the first nvalid of them real
-  auto attend_tile = [&](const uint4 (&kk)[KS], const uint4 (&vv)[4], int kb, int nvalid) {
-    // V^T block into LDS: row e of the block = V[4 kg .. 4 kg + 3][8 dg + e]
-    if (l < VBL) {
-      const uint32_t* x = reinterpret_cast<const uint32_t*>(vv);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;
-        const uint32_t w01 = __builtin_amdgcn_perm(x[4 + e / 2], x[e / 2], sel);
-        const uint32_t w23 = __builtin_amdgcn_perm(x[12 + e / 2], x[8 + e / 2], sel);
-        *reinterpret_cast<uint2*>(&vt[(dg * 9 + e) * 16 + kg * 4]) = make_uint2(w01, w23);  // row 8 dg + e
-      }
-    }
-    dm_f32x4 s = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) s = mma_qk(kk[ks], qB[ks], s);
+  // softmax of a tile's scores (lane: keys 4 lq + r of query lr), the first
+  // nvalid keys real; returns the probabilities rounded to bf16
+  auto soft = [&](const dm_f32x4& s, int nvalid) __attribute__((always_inline)) -> uint2 {
     float x[4], lmax = -INFINITY;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -275,50 +284,69 @@ __global__ void __launch_bounds__(256) decode_mfma_kernel(DecodeArgs args, const
       p[r] = __builtin_amdgcn_exp2f(x[r] - mref);  // 0 for keys past the tile's real ones
       lsum += p[r];
     }
-    const uint2 pb = make_uint2(dm_cvt_bf16x2(p[0], p[1]), dm_cvt_bf16x2(p[2], p[3]));
-    asm volatile("" ::: "memory");  // the wave's V^T writes come before its reads (LDS is in order per wave)
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt) {
-      const int r = dt * 16 + lr;
-      const uint2 a = *reinterpret_cast<const uint2*>(&vt[(r + (r >> 3)) * 16 + 4 * lq]);
-      acc[dt] = mma_pv(a, pb, acc[dt]);
-    }
-    asm volatile("" ::: "memory");  // ... and before the next tile's writes
+    return make_uint2(dm_cvt_bf16x2(p[0], p[1]), dm_cvt_bf16x2(p[2], p[3]));
   };
 
-  // three register sets: the wave's next two tiles are in flight while one
-  // is attended (a 192-key split is requested entirely before its first
-  // tile is attended)
-  for (int ti = w; ti < ntile; ti += 12) {
-    attend_tile(kA, vA, k0 + ti * 16, min(16, kend - k0 - ti * 16));
-    load_tile(ti + 12, kA, vA);
-    if (ti + 4 >= ntile) break;
-    attend_tile(kB, vB, k0 + (ti + 4) * 16, min(16, kend - k0 - (ti + 4) * 16));
-    load_tile(ti + 16, kB, vB);
-    if (ti + 8 >= ntile) break;
-    attend_tile(kC, vC, k0 + (ti + 8) * 16, min(16, kend - k0 - (ti + 8) * 16));
-    load_tile(ti + 20, kC, vC);
-  }
-
-  if (owns_new) __syncthreads();  // the new token is in LDS (a block-uniform branch)
-  if (owns_new && w == (ntile & 3)) {
-    // the new token as a one-key tile: key row 0, V block of keys 0 .. 3
-    uint4 kn[KS], vn[4];
+  for (int ti = 0; ti < n; ++ti) {
+    if (ti + NB - 1 < n) {
+      wait_lds();  // the buffer's last reads (the prologue's rows, then the tile before) have returned
+      const Entry e = nx;
+      nx = entry(ti + NB);
+      issue(ti + NB - 1, e);
+    }
+    wait_tiles(min(NB - 1, n - 1 - ti));  // this tile has landed; the later ones stay in flight
+    const bf16_t* T = reinterpret_cast<const bf16_t*>(ring + (ti & (NB - 1)) * TILE);
+    uint4 kk[KS];
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-      kn[ks] = lr == 0 ? *reinterpret_cast<const uint4*>(&s_newk[ks * 32 + lq * 8]) : make_uint4(0u, 0u, 0u, 0u);
-    vn[0] = kg == 0 ? *reinterpret_cast<const uint4*>(&s_newv[dg * 8]) : make_uint4(0u, 0u, 0u, 0u);
-    vn[1] = vn[2] = vn[3] = make_uint4(0u, 0u, 0u, 0u);
-    attend_tile(kn, vn, pos, 1);
+    for (int ks = 0; ks < KS; ++ks) kk[ks] = ld16(&T[(lr * NC + ((ks * 4 + lq) ^ (lr % NC))) * 8]);
+    // V^T fragment dt: lane (lr, lq) needs V[4 lq + e][16 dt + lr], e = 0..3; in
+    // the transpose read, lane lr of group lq addresses row 4 lq + lr / 4, dims
+    // 16 dt + 4 (lr % 4) .. + 3
+    uint2 va[DT];
+    {
+      const int vr = 4 * lq + (lr >> 2), vsw = 2 * (vr % (NC / 2));
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+        va[dt] = ld_tr8(&T[16 * D + (vr * NC + ((2 * dt + ((lr & 3) >> 1)) ^ vsw)) * 8 + (lr & 1) * 4]);
+    }
+    dm_f32x4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) s = mma_qk(kk[ks], qB[ks], s);
+    const uint2 pb = soft(s, min(16, kend - k0 - (w + 4 * ti) * 16));
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) acc[dt] = mma_pv(va[dt], pb, acc[dt]);
   }
 
-  // ---- merge the four waves: per query, M over the waves, each wave's
-  // output and sum weighted by 2^(m - M)
-  lsum = sum_rows4(lsum);
-  if (lr < G) {
+  if (new_wave) {
+    // the new token: into its cache slot, and attended as a one-key tile (key
+    // row 0, value element (key 0) of each dim)
+    if (l < NC) {
+      const int64_t off = new_token_offset<PAGED>(cv, layer, seq, hk, pos, npage) + l * 8;
+      st16(reinterpret_cast<bf16_t*>(cv.k) + off, ld16(&s_newk[l * 8]));
+      st16(reinterpret_cast<bf16_t*>(cv.v) + off, ld16(&s_newv[l * 8]));
+    }
+    dm_f32x4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const uint4 kn = ld16(&s_newk[ks * 32 + lq * 8]);
+      s = mma_qk(lr == 0 ? kn : make_uint4(0u, 0u, 0u, 0u), qB[ks], s);
+    }
+    const uint2 pb = soft(s, 1);
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
-      *reinterpret_cast<float4*>(&s_buf[(w * G + lr) * D + dt * 16 + 4 * lq]) =
+      acc[dt] = mma_pv(make_uint2(lq == 0 ? (uint32_t)s_newv[dt * 16 + lr] : 0u, 0u), pb, acc[dt]);
+  }
+
+  // ---- merge the four waves: per query, M over the waves, each wave's output
+  // and sum weighted by 2^(m - M).  A wave's outputs go into its own ring, which
+  // no other wave reads before the barrier.
+  lsum = sum_rows4(lsum);
+  wait_lds();
+  if (lr < G) {
+    float* o = reinterpret_cast<float*>(ring);
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+      *reinterpret_cast<float4*>(&o[lr * D + dt * 16 + 4 * lq]) =
           make_float4(acc[dt][0], acc[dt][1], acc[dt][2], acc[dt][3]);
     if (lq == 0) {
       s_wm[w][lr] = mref;
@@ -336,7 +364,7 @@ __global__ void __launch_bounds__(256) decode_mfma_kernel(DecodeArgs args, const
     for (int w2 = 0; w2 < 4; ++w2) {
       const float m = s_wm[w2][j];
       const float f = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - M);
-      const float2 o = *reinterpret_cast<const float2*>(&s_buf[(w2 * G + j) * D + d]);
+      const float2 o = *reinterpret_cast<const float2*>(s_ring + w2 * (NB * TILE) + (j * D + d) * 4);
       L = fmaf(s_wl[w2][j], f, L);
       a0 = fmaf(o.x, f, a0);
       a1 = fmaf(o.y, f, a1);
@@ -345,22 +373,31 @@ __global__ void __launch_bounds__(256) decode_mfma_kernel(DecodeArgs args, const
                          part_o, part_ml, d, a0, a1, M, L);
   }
   if (nsplit == 1) return;
-  merge_splits<bf16_t, D, G, NBUF>(args, i, hk, slot0, nsplit, Hkv, Hq, out, part_o, part_ml, count, s_buf, s_mt,
-                                   s_lt, &s_last);
+  merge_splits<bf16_t, D, G>(args, i, hk, slot0, nsplit, Hkv, Hq, out, part_o, part_ml, count,
+                                   reinterpret_cast<float*>(s_ring), s_mt, s_lt, &s_last);
 }
 
+// ring: 4 (128 KB of LDS at D 128, one block per CU) where the plan gives every
+// CU at most one short split: all of it is requested at once.  2 (two blocks per
+// CU) for more keys; those launches also read with the nontemporal hint, the
+// keys always and the values unless the tasks share them in the library: whole
+// rows read that way arrive at 6.9 TB/s against 6.2 (measured on the kernel, with
+// against without: 796 MB 2001 / 2184 us, 369 MB 506 / 553, 131 MB 439 / 460, 44
+// MB 425 / 432 per pass; 17.5 MB 1218 / 1201, so not there; shared values
+// 1125 / 1097).
 int launch_decode_mfma(const DecodeArgs& args, const void* q, const void* k, const void* v, const CacheView& cv,
                        int layer, const float2* rope, int Hq, void* out, float* part_o, float* part_ml,
-                       int* count, hipStream_t s, KTime tm) {
+                       int* count, int ring, hipStream_t s, KTime tm) {
   if (args.n == 0) return 0;
   const int g = Hq / cv.n_kv_heads;
   dim3 grid(args.max_split, args.n, cv.n_kv_heads);
-#define DM1(DD, GG, PG)                                                                                       \
-  hipExtLaunchKernelGGL((decode_mfma_kernel<DD, GG, PG>), grid, dim3(256), 0, s, tm.start, tm.stop, 0, args,   \
+#define DM2(DD, GG, PG, NB)                                                                                   \
+  hipExtLaunchKernelGGL((decode_mfma_kernel<DD, GG, PG, NB>), grid, dim3(256), 0, s, tm.start, tm.stop, 0, args,   \
                         (const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v, cv, rope, (bf16_t*)out, part_o,   \
                         part_ml, count, layer)
+#define DM1(DD, GG, PG) { if (ring == 4) DM2(DD, GG, PG, 4); else DM2(DD, GG, PG, 2); }
 #define DM(DD, GG)                                                                                            \
-  if (cv.page_size) DM1(DD, GG, true);                                                                        \
+  if (cv.page_size) DM1(DD, GG, true)                                                                         \
   else DM1(DD, GG, false)
 #define DMG(DD)                                                                                               \
   switch (g) {                                                                                                \
@@ -375,6 +412,7 @@ int launch_decode_mfma(const DecodeArgs& args, const void* q, const void* k, con
 #undef DMG
 #undef DM
 #undef DM1
+#undef DM2
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? 0 : (int)e;
 }

@@ -248,10 +248,11 @@ int launch_decode(int dtype, const DecodeArgs& args, const void* q, const void* 
                   hipStream_t s, KTime tm = {});
 
 // The same step on matrix cores for bf16 caches and query groups of up to 16
-// heads (same arguments; -1 for a group size it has no instance for).
+// heads (same arguments; -1 for a group size it has no instance for).  ring:
+// tiles in each wave's LDS ring, 4 or 2.
 int launch_decode_mfma(const DecodeArgs& args, const void* q, const void* k, const void* v, const CacheView& cv,
                        int layer, const float2* rope, int Hq, void* out, float* part_o, float* part_ml,
-                       int* count, hipStream_t s, KTime tm = {});
+                       int* count, int ring, hipStream_t s, KTime tm = {});
 
 // Static scratch of the allocation-free decode entry point (noalloc.hip):
 // arrival counters for kMaxDecodeSeqs sequences x kNoAllocMaxKvHeads kv heads,

@@ -24,3 +24,29 @@ def test_graft_plan_by_value_and_uploaded(n_seqs, n_segs, page, alias):
     segs = [[(s + j) % len(lengths) for j in range(n_segs)] for s in range(n_seqs)]
     w = synth.custom(synth.Shape(2, 8, 2, 64, 1e4, "bf16"), 3, lengths, segs, 5, 1, page_size=page)
     parity.run_pipeline(w, [1], 1, [0, n_seqs - 1], alias=alias)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("g,page,alias", [(1, 0, False), (2, 16, True), (4, 16, False), (8, 0, False), (16, 16, True)])
+@pytest.mark.parametrize("ctx", ["edges", "long"])
+def test_decode_ring_and_merge(d, g, page, alias, ctx):
+    """Both rings of the bf16 decode (one short split per CU; two blocks per CU past 256 keys for
+    each) at ragged lengths: fewer tiles than waves, a partial tile, a split that holds the new
+    token alone, one sequence with splits beyond one batch of the merge's loads."""
+    if ctx == "edges":
+        hkv, lens = 2, [1, 15, 63, 64, 127, 800, 191]
+    else:
+        hkv, lens = (8, [8301, 17, 1535]) if g < 16 else (4, [16601, 17, 1535])  # over 65536 (key, kv head) pairs
+    # two fresh tokens precede the decode steps: segment lengths two short
+    segs = [[i] for i in range(len(lens))]
+    w = synth.custom(synth.Shape(1, hkv * g, hkv, d, 1e6, "bf16"), 5, [max(1, n - 2) for n in lens], segs, 2, 3,
+                     page_size=page)
+    parity.run_pipeline(w, [0], 3, list(range(len(lens))), alias=alias)
+
+
+@pytest.mark.parametrize("g,d", [(1, 64), (2, 128), (8, 64), (16, 128)])
+def test_fp32_decode_merge(g, d):
+    """The fp32 step's split merge over its chunk counts (16 to 512 16-byte chunks a split), with a
+    sequence of one split and one of many."""
+    w = synth.custom(synth.Shape(1, 2 * g, 2, d, 1e4, "f32"), 5, [40, 3000], [[0], [1]], 2, 2, page_size=0)
+    parity.run_pipeline(w, [0], 2, [0, 1])

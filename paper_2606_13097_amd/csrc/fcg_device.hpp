@@ -115,13 +115,23 @@ __device__ __forceinline__ uint32_t lds_addr(const void* p) {
 __device__ __forceinline__ void dma16(const void* g, uint32_t lds) {
   asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "{m0}"(lds) : "memory");
 }
-// the same from a scalar base plus a lane offset; NT: with the nontemporal hint
+// the same from a scalar base plus a lane offset; NT: with the nontemporal hint.
+// The base may come from a vector instruction (v_readfirstlane, the compiler's or
+// uniform_ptr's): a vector memory instruction may read such a scalar register
+// only five wait states later, and the compiler does not look into the assembly,
+// hence s_nop 4.
 template <bool NT = false>
 __device__ __forceinline__ void dma16s(const void* base, uint32_t off, uint32_t lds) {
   if (NT)
-    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(off), "s"(base), "{m0}"(lds) : "memory");
+    asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(off), "s"(base), "{m0}"(lds) : "memory");
   else
-    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "{m0}"(lds) : "memory");
+    asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "{m0}"(lds) : "memory");
+}
+// a wave-uniform pointer that the compiler may hold in vector registers, as a scalar one
+__device__ __forceinline__ const void* uniform_ptr(const void* p) {
+  const uint64_t x = (uint64_t)(uintptr_t)p;
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)x), hi = __builtin_amdgcn_readfirstlane((uint32_t)(x >> 32));
+  return (const void*)(uintptr_t)((uint64_t)hi << 32 | lo);
 }
 // s_waitcnt vmcnt(N): at most N of this wave's vector memory operations remain
 template <int N>

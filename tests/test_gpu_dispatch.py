@@ -50,3 +50,15 @@ def test_fp32_decode_merge(g, d):
     sequence of one split and one of many."""
     w = synth.custom(synth.Shape(1, 2 * g, 2, d, 1e4, "f32"), 5, [40, 3000], [[0], [1]], 2, 2, page_size=0)
     parity.run_pipeline(w, [0], 2, [0, 1])
+
+
+@pytest.mark.parametrize("d,g", [(64, 2), (128, 4), (128, 16)])
+@pytest.mark.parametrize("page,alias", [(0, False), (16, False), (16, True)])
+@pytest.mark.parametrize("n_fresh", [1, 40, 131])
+def test_prefill_tile_addresses(d, g, page, alias, n_fresh):
+    """Key tiles wholly cached (addressed from a scalar base per load) and tiles that hold fresh
+    keys or end the split (per lane), with contexts around multiples of the 64-key tile."""
+    lens = [1, 63, 64, 65, 127, 449]
+    w = synth.custom(synth.Shape(1, 2 * g, 2, d, 1e6, "bf16"), 7, lens, [[i] for i in range(len(lens))], n_fresh, 1,
+                     page_size=page)
+    parity.run_pipeline(w, [0], 1, list(range(len(lens))), alias=alias)

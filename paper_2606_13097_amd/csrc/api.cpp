@@ -356,11 +356,9 @@ size_t stage_row(const fcg_cache* c, int32_t seq, Blob* blob) {
 void stage_pages(fcg_cache* c, const std::vector<std::pair<int32_t, int32_t>>& new_pages, Blob* blob,
                  std::vector<std::pair<int32_t, size_t>>* rows) {
   c->plan.map_pages(new_pages);
-  std::vector<int32_t> seqs;
-  for (auto& sl : new_pages) seqs.push_back(sl.first);
-  std::sort(seqs.begin(), seqs.end());
-  seqs.erase(std::unique(seqs.begin(), seqs.end()), seqs.end());
-  for (int32_t s : seqs) rows->push_back({s, stage_row(c, s, blob)});
+  int32_t last = -1;  // new pages come in (sequence, logical page) order
+  for (auto& sl : new_pages)
+    if (sl.first != last) rows->push_back({last = sl.first, stage_row(c, sl.first, blob)});
 }
 
 // Upload a plan: the staged page rows (at the front of the blob, in the order

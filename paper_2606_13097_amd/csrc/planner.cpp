@@ -24,7 +24,23 @@ Planner::Planner(int32_t n_layers, int32_t n_seqs, int32_t max_tokens, int32_t p
   cnt_.assign((size_t)S_ * L_, 0);
   page_table_.assign((size_t)S_ * NLP_, -1);
   valias_.assign((size_t)S_ * NLP_, -1);
-  for (int32_t p = 0; p < NP_; ++p) free_.insert(free_.end(), p);
+  free_.assign((size_t)(NP_ + 63) / 64, ~0ull);
+  if (NP_ & 63) free_.back() = (1ull << (NP_ & 63)) - 1;
+  n_free_ = NP_;
+}
+
+int32_t Planner::take_page() {
+  while (!free_[low_]) ++low_;
+  const int32_t p = low_ * 64 + __builtin_ctzll(free_[low_]);
+  free_[low_] &= free_[low_] - 1;
+  --n_free_;
+  return p;
+}
+
+void Planner::return_page(int32_t p) {
+  free_[p >> 6] |= 1ull << (p & 63);
+  low_ = std::min(low_, p >> 6);
+  ++n_free_;
 }
 
 bool Planner::written(int32_t seq, int32_t layer, int32_t pos) const {
@@ -58,10 +74,10 @@ fcg_status Planner::collect_pages(const std::vector<std::pair<int32_t, int32_t>>
   std::vector<std::pair<int32_t, int32_t>> v;
   for (auto& sl : seq_lpage)
     if (page_table_[(size_t)sl.first * NLP_ + sl.second] < 0) v.push_back(sl);
-  std::sort(v.begin(), v.end());
+  if (!std::is_sorted(v.begin(), v.end())) std::sort(v.begin(), v.end());
   v.erase(std::unique(v.begin(), v.end()), v.end());
-  if (v.size() > free_.size()) {
-    *msg = fmt("%lld new pages needed, %lld free", (long long)v.size(), (long long)free_.size());
+  if ((int64_t)v.size() > n_free_) {
+    *msg = fmt("%lld new pages needed, %lld free", (long long)v.size(), (long long)n_free_);
     return FCG_ENOMEM;
   }
   *new_pages = std::move(v);
@@ -165,11 +181,7 @@ fcg_status Planner::check_decode(int32_t layer, int32_t n, const int32_t* seq, s
 }
 
 void Planner::map_pages(const std::vector<std::pair<int32_t, int32_t>>& new_pages) {
-  for (auto& sl : new_pages) {
-    int32_t p = *free_.begin();
-    free_.erase(free_.begin());
-    page_table_[(size_t)sl.first * NLP_ + sl.second] = p;
-  }
+  for (auto& sl : new_pages) page_table_[(size_t)sl.first * NLP_ + sl.second] = take_page();
 }
 
 void Planner::mark(int32_t seq, int32_t layer, int32_t pos) {
@@ -183,8 +195,20 @@ void Planner::mark(int32_t seq, int32_t layer, int32_t pos) {
 }
 
 void Planner::mark_all_layers(int32_t seq, int32_t dst, int32_t len) {
-  for (int32_t l = 0; l < L_; ++l)
-    for (int32_t p = dst; p < dst + len; ++p) mark(seq, l, p);
+  if (len <= 0) return;
+  for (int32_t l = 0; l < L_; ++l) {
+    uint64_t* w = bits(seq, l);
+    int32_t added = 0;
+    for (int32_t p = dst; p < dst + len;) {  // a word at a time
+      const int32_t lo = p & 63, hi = std::min(64, lo + (dst + len - p));
+      const uint64_t mask = (hi == 64 ? ~0ull : ((1ull << hi) - 1)) & ~((1ull << lo) - 1);
+      added += __builtin_popcountll(mask & ~w[p >> 6]);
+      w[p >> 6] |= mask;
+      p += hi - lo;
+    }
+    cnt_[idx(seq, l)] += added;
+    len_[idx(seq, l)] = std::max(len_[idx(seq, l)], dst + len);
+  }
 }
 
 void Planner::alias_pages(int32_t seq, int32_t dst, int32_t len, int64_t lib_tok0) {
@@ -202,7 +226,7 @@ void Planner::reset(int32_t seq) {
   }
   for (int32_t lp = 0; lp < NLP_; ++lp) {
     int32_t& e = page_table_[(size_t)seq * NLP_ + lp];
-    if (e >= 0) { free_.insert(e); e = -1; }
+    if (e >= 0) { return_page(e); e = -1; }
   }
 }
 
@@ -215,25 +239,22 @@ void Planner::truncate(int32_t seq, int32_t pos, std::vector<Unalias>* unalias) 
     }
   }
   for (int32_t l = 0; l < L_; ++l) {
+    int32_t &len = len_[idx(seq, l)], &cnt = cnt_[idx(seq, l)];
+    if (len <= pos) continue;  // nothing at or past pos
     uint64_t* b = bits(seq, l);
-    for (int32_t wi = 0; wi < W_; ++wi) {
-      const int32_t lo = wi * 64;
-      if (lo >= pos) b[wi] = 0;
-      else if (lo + 64 > pos) b[wi] &= (1ull << (pos - lo)) - 1;
+    for (int32_t wi = pos >> 6; wi <= (len - 1) >> 6; ++wi) {
+      const uint64_t keep = wi == pos >> 6 ? (1ull << (pos & 63)) - 1 : 0;
+      cnt -= __builtin_popcountll(b[wi] & ~keep);
+      b[wi] &= keep;
     }
-    int32_t cnt = 0, len = 0;
-    for (int32_t wi = 0; wi < W_; ++wi)
-      if (b[wi]) {
-        cnt += __builtin_popcountll(b[wi]);
-        len = wi * 64 + 64 - __builtin_clzll(b[wi]);
-      }
-    cnt_[idx(seq, l)] = cnt;
-    len_[idx(seq, l)] = len;
+    int32_t wi = pos >> 6;  // the highest position left
+    while (wi >= 0 && !b[wi]) --wi;
+    len = wi < 0 ? 0 : wi * 64 + 64 - __builtin_clzll(b[wi]);
   }
   if (P_)
     for (int32_t lp = (pos + P_ - 1) / P_; lp < NLP_; ++lp) {
       int32_t& e = page_table_[(size_t)seq * NLP_ + lp];
-      if (e >= 0) { free_.insert(e); e = -1; }
+      if (e >= 0) { return_page(e); e = -1; }
       valias_[(size_t)seq * NLP_ + lp] = -1;
     }
 }

@@ -9,7 +9,6 @@
 #pragma once
 
 #include <cstdint>
-#include <set>
 #include <string>
 #include <utility>
 #include <vector>
@@ -92,7 +91,14 @@ class Planner {
   std::vector<int32_t> len_, cnt_;   // [S][L]
   std::vector<int32_t> page_table_;  // [S][NLP], -1 = unmapped
   std::vector<int32_t> valias_;      // [S][NLP], library token or -1
-  std::set<int32_t> free_;           // free physical pages, ascending
+  // Free physical pages as bits; low_ is at most the word of the lowest one, so
+  // taking it scans on from there.  (A std::set here, with one node per page, and
+  // marking position by position took 1.9 ms of host time to reset and graft 32
+  // tasks of ~6K tokens in 4 layers, against 0.85 ms of GPU time.)
+  std::vector<uint64_t> free_;
+  int32_t n_free_ = 0, low_ = 0;
+  int32_t take_page();          // the lowest free page (there is one)
+  void return_page(int32_t p);
 };
 
 }  // namespace fcg

@@ -222,13 +222,16 @@ __global__ void __launch_bounds__(WAVES * 64, WAVES == 4 ? 2 : 1) attn_prefill_m
   // of a paged cache once per instruction instead of per lane (the loop's vector
   // and matrix instructions do not overlap, so each costs its issue time:
   // 32 paged tasks x 32 tokens 736 -> 700 us for 4 layers, 34B shape 2774 ->
-  // 2678 for 2, 16.7K context 1535 -> 1515).
+  // 2678 for 2, 16.7K context 1535 -> 1515).  Not in contiguous launches of
+  // 16-row waves: those are bound by latency, not by issue (7B patch: 602 us a
+  // pass with it, 595 without).
+  constexpr bool BASED = PAGED || RT > 1;
   constexpr int RI = 64 / NC;                       // rows of one instruction
   const int lane_row = lane / NC * D * 2;           // byte offset of the lane's row in the instruction's
   const int lane_k = lane % NC ^ lane / NC, lane_v = lane % NC ^ Tile::swz_v(lane / NC);
   auto issue_to = [&](int tile, Tile& B) __attribute__((always_inline)) {
     const int kb = k0 + tile * kBN;
-    if ((!PAGED || window) && kb + kBN <= (FUSED ? min(kend, rb.f0) : kend)) {
+    if (BASED && (!PAGED || window) && kb + kBN <= (FUSED ? min(kend, rb.f0) : kend)) {
 #pragma unroll
       for (int u = 0; u < DPT; ++u) {
         const bool isv = WAVES * u >= NC;

@@ -955,7 +955,7 @@ fcg_status run_attention(fcg_cache* c, int32_t layer, const std::vector<TokenMet
   const int g = d.n_q_heads / d.n_kv_heads;
   const bool mfma = d.dtype == FCG_BF16;
   // row blocks: consecutive ranks of one sequence, at most 256 (or 128) query
-  // rows (MFMA) or one token
+  // rows (MFMA) or 4, 2 or 1 tokens
   auto row_blocks = [&](int max_rank) {
     std::vector<std::pair<int, int>> rb;  // (rank0, n_rank)
     for (int r = 0; r < n;) {
@@ -982,7 +982,8 @@ fcg_status run_attention(fcg_cache* c, int32_t layer, const std::vector<TokenMet
     }
     r0 = r1;
   }
-  std::vector<std::pair<int, int>> rblocks = row_blocks(mfma ? std::max(1, 256 / g) : 1);
+  int rows_tokens = attn_rows_tokens(g, d.head_dim);  // fp32: tokens of a row block
+  std::vector<std::pair<int, int>> rblocks = row_blocks(mfma ? std::max(1, 256 / g) : rows_tokens);
   // MFMA: unless 256-row blocks alone fill the chip twice, use 128-row blocks
   // of 4 waves sized to run two per CU (one block's softmax beside the other's
   // matrix work), with the key splits planned for 512 blocks
@@ -992,13 +993,27 @@ fcg_status run_attention(fcg_cache* c, int32_t layer, const std::vector<TokenMet
   // once: one split length (in tiles) for the call, the smallest whose blocks
   // fit one per CU (two in pair mode); at most 256 splits per row block (the
   // merge table)
-  const int tile = mfma ? 64 : 256;
+  // (fp32: tiles of 128 keys, two steps of a block, planned for four blocks per
+  // CU; 256-key tiles and 256 blocks left 80 tokens x ~1.4K keys at 76 us a call
+  // against 53)
+  const int tile = mfma ? 64 : 128;
   std::vector<int64_t> rb_tiles;
   int64_t total_tiles = 0, max_tiles = 0;
-  for (auto& rb : rblocks) {
-    rb_tiles.push_back((meta[rb.first + rb.second - 1].pos + tile) / tile);
-    total_tiles += rb_tiles.back();
-    max_tiles = std::max(max_tiles, rb_tiles.back());
+  auto count_tiles = [&]() {
+    rb_tiles.clear();
+    total_tiles = max_tiles = 0;
+    for (auto& rb : rblocks) {
+      rb_tiles.push_back((meta[rb.first + rb.second - 1].pos + tile) / tile);
+      total_tiles += rb_tiles.back();
+      max_tiles = std::max(max_tiles, rb_tiles.back());
+    }
+  };
+  count_tiles();
+  // fewer tokens a block while its finest split leaves the chip short of two
+  // blocks per CU (512 or 1024 blocks: within 2% of each other)
+  while (!mfma && rows_tokens > 1 && total_tiles * d.n_kv_heads < 512) {
+    rblocks = row_blocks(rows_tokens /= 2);
+    count_tiles();
   }
   const int min_tiles = mfma ? 2 : 1;
   auto split_tiles = [&](int64_t target) {
@@ -1012,7 +1027,7 @@ fcg_status run_attention(fcg_cache* c, int32_t layer, const std::vector<TokenMet
     }
     return per;
   };
-  int64_t per = split_tiles(pair ? 512 : 256);
+  int64_t per = split_tiles(!mfma ? 1024 : pair ? 512 : 256);
   // pair mode with splits under 8 tiles: the call is bound by latency, not by
   // the matrix work, and planning for one block per CU halves the splits the
   // combine merges (7B patch: call 35 -> 31 us, the attention kernel unchanged).
@@ -1071,7 +1086,7 @@ fcg_status run_attention(fcg_cache* c, int32_t layer, const std::vector<TokenMet
   // MFMA blocks of 8 waves (256 rows) when some row block needs more than 4 waves
   int max_rows = 0;
   for (auto& rb : rblocks) max_rows = std::max(max_rows, rb.second * g);
-  const int stride_rows = mfma ? (max_rows > 128 ? 256 : 128) : g;  // pair: max_rows <= 128
+  const int stride_rows = mfma ? (max_rows > 128 ? 256 : 128) : rows_tokens * g;  // pair: max_rows <= 128
   // workspaces first: a failure here leaves the layout untouched
   const size_t qbytes = (size_t)d.n_kv_heads * n * g * d.head_dim * esize(d.dtype);
   if (!fused)
@@ -1117,15 +1132,15 @@ fcg_status run_attention(fcg_cache* c, int32_t layer, const std::vector<TokenMet
       if (rc) break;
     }
   } else
-    rc = launch_attn_rows(d.dtype, (const AttnItem*)(dev + o_items), (int)items.size(), dmeta, c->qws, n * g, cv,
-                          layer, d.n_q_heads, out, part_o, part_ml, stride_rows, s, KTime{e_attn0, e_attn1});
+    rc = launch_attn_rows((const AttnItem*)(dev + o_items), (int)items.size(), dmeta, c->qws, n * g, cv, layer,
+                          d.n_q_heads, out, part_o, part_ml, stride_rows, rows_tokens, s, KTime{e_attn0, e_attn1});
   if (rc) return hip_fail((hipError_t)rc, "attention launch");
   for (size_t c0 = 0; c0 < comb.size(); c0 += kCombMaxItems) {  // merge plans by value
     CombineArgs ca{};
     ca.n_items = (int32_t)std::min<size_t>(kCombMaxItems, comb.size() - c0);
     std::copy(comb.begin() + c0, comb.begin() + c0 + ca.n_items, ca.item);
     const bool last = c0 + kCombMaxItems >= comb.size();
-    rc = launch_combine(d.dtype, ca, dmeta, d.n_q_heads, d.n_kv_heads, d.head_dim, part_o, part_ml, stride_rows,
+    rc = launch_combine(ca, dmeta, d.n_q_heads, d.n_kv_heads, d.head_dim, part_o, part_ml, stride_rows,
                         out, s, mfma, KTime{nullptr, last ? e_call1 : nullptr});
     if (rc) return hip_fail((hipError_t)rc, "combine launch");
   }

@@ -1,157 +1,191 @@
-// Vector-ALU attention for gfx950: one query token (its g query heads sharing
-// one kv head) per block, over one split [k0, k1) of its causal key range.
-// Used for decode steps (one query per sequence: HBM-bound, about 4 FLOP per
-// byte at g = 4, so matrix cores would idle) and for fp32 caches.
+// Vector-ALU attention for gfx950, fp32 caches: the g query heads of one kv head
+// for R consecutive tokens of a sequence per block, over one split [k0, k1) of
+// the key positions (fp32 stays in the vector units: the rate of a few tokens
+// over a cache is set by loads and latency).
 //
-// Lane layout: a key row of D elements is split into 16-byte vectors; LPK =
-// D / VEC lanes hold one key, so a wave covers 64 / LPK keys per step and
-// every load is a coalesced 16-byte vector.  Scores are reduced across the LPK
-// lanes of a key with DPP (quad_perm, row_half_mirror, row_mirror).  Each lane
-// keeps its own running max / sum / output (online softmax in base 2: the
-// query is pre-scaled by log2(e) / sqrt(D)); the 256 lanes are merged through
-// LDS at the end of the block.  A block that covers the whole range writes the
+// Lane layout: 16 lanes hold a key row (16-byte vectors), so a block's 16 slots
+// cover 16 keys per load instruction, every load a coalesced 16-byte vector; a
+// step takes U keys per slot, their loads issued together.  Scores are reduced
+// across a key's 16 lanes with DPP (quad_perm, row_half_mirror, row_mirror).
+// Each slot keeps its own running max / sum / output per query row (online
+// softmax in base 2: the query is pre-scaled by log2(e) / sqrt(D)), rescaled
+// once per step.  At the end the four slots of a wave merge by lane swaps, the
+// four waves through LDS.  A block that covers the whole range writes the
 // normalised output; otherwise it writes a partial (max, sum, unnormalised
 // output) that the combine kernel merges.
+//
+// What bounds it: many tokens, the rows' loads through L2 (512 tokens over ~4K
+// keys of 4 kv heads, g 8, D 128: 930 us a call, about 9 TB/s of rows); few, the chain of
+// upload, append, attention and merge launches (64 tokens over ~2K keys: a pass
+// of four such calls and 16 decode steps 287 -> 209 us).  Before, a block held one
+// token, a lane had one key's loads in flight and 256 blocks were planned, and
+// sixteen slots' outputs were added through LDS row by row behind two barriers
+// each.
+#include <type_traits>
+
 #include "fcg_device.hpp"
 #include "kernels.hpp"
 
 namespace fcg {
 
-template <int CTRL>
-__device__ __forceinline__ float dpp(float x) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, false));
-}
-
-// Sum over groups of LPK consecutive lanes (LPK in 1, 2, 4, 8, 16); every lane gets the sum.
-template <int LPK>
-__device__ __forceinline__ float group_sum(float x) {
-  if (LPK >= 2) x += dpp<0xB1>(x);   // quad_perm [1,0,3,2]
-  if (LPK >= 4) x += dpp<0x4E>(x);   // quad_perm [2,3,0,1]
-  if (LPK >= 8) x += dpp<0x141>(x);  // row_half_mirror
-  if (LPK >= 16) x += dpp<0x140>(x); // row_mirror
+// Sum over the 16 lanes of a DPP row; every lane gets the sum.
+__device__ __forceinline__ float sum_lanes16(float x) {
+  x += dpp_f32<kDppXor1>(x);
+  x += dpp_f32<kDppXor2>(x);
+  x += dpp_f32<kDppHalfMirror>(x);
+  x += dpp_f32<kDppMirror>(x);
   return x;
 }
 
-template <typename T, int D, int G>
+template <int D, int G, int R>
 __global__ void __launch_bounds__(256) attn_rows_kernel(const AttnItem* __restrict__ items,
                                                         const TokenMeta* __restrict__ meta,
-                                                        const T* __restrict__ qws, int rows_ws, CacheView cv,
-                                                        int layer, int Hq, T* __restrict__ out,
+                                                        const float* __restrict__ qws, int rows_ws, CacheView cv,
+                                                        int layer, int Hq, float* __restrict__ out,
                                                         float* __restrict__ part_o, float* __restrict__ part_ml,
                                                         int part_stride_rows) {
-  constexpr int VEC = Store<T>::VEC;
-  constexpr int NV = (D / VEC > 16) ? (D / VEC) / 16 : 1;  // 16-byte vectors per lane
-  constexpr int DPL = VEC * NV;                              // dims per lane
-  constexpr int LPK = D / DPL;                               // lanes per key (<= 16)
-  constexpr int SLOTS = 256 / LPK;                           // keys per block step
-  static_assert(LPK <= 16, "a key must fit one DPP row");
-  __shared__ float s_m[SLOTS][G], s_l[SLOTS][G];
-  __shared__ float s_o[SLOTS][DPL][LPK];
-  __shared__ float s_M[G], s_L[G];
+  constexpr int NV = D / 64;      // 16-byte vectors per lane and row: dims 64 nv + 4 chunk .. + 3
+  constexpr int DPL = 4 * NV;     // dims per lane
+  constexpr int ROWS = G * R;     // query rows
+  constexpr int U = ROWS * DPL <= 32 ? 4 : ROWS * DPL <= 64 ? 2 : 1;  // keys per slot and step (registers)
+  constexpr int STEP = 16 * U;
+  __shared__ __align__(16) float s_o[4][ROWS][D];
+  __shared__ float s_m[4][ROWS], s_l[4][ROWS];
 
   const AttnItem it = items[blockIdx.x];
   const int hk = blockIdx.y;
   const int Hkv = cv.n_kv_heads;
-  const TokenMeta m = meta[it.rank0];
-  const int t = threadIdx.x;
-  const int chunk = t % LPK;
-  const int slot = t / LPK;
+  const int t = threadIdx.x, w = t >> 6;
+  const int chunk = t & 15, slot = t >> 4;
   const float qscale = 1.4426950408889634f / sqrtf((float)D);
 
-  float q[G][DPL];
+  // a block of fewer than R tokens repeats its last one (not written)
+  int pos[R];
 #pragma unroll
-  for (int j = 0; j < G; ++j)
+  for (int r = 0; r < R; ++r) pos[r] = meta[it.rank0 + min(r, it.n_rank - 1)].pos;
+  float q[ROWS][DPL];
+#pragma unroll
+  for (int j = 0; j < ROWS; ++j)
 #pragma unroll
     for (int nv = 0; nv < NV; ++nv) {
-      float x[VEC];
-      Store<T>::unpack(
-          ld16(qws + ((int64_t)hk * rows_ws + (int64_t)it.rank0 * G + j) * D + chunk * DPL + nv * VEC), x);
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) q[j][nv * VEC + e] = x[e] * qscale;
+      const int64_t row = (int64_t)hk * rows_ws + (int64_t)(it.rank0 + min(j / G, it.n_rank - 1)) * G + j % G;
+      const float4 x = *reinterpret_cast<const float4*>(qws + row * D + nv * 64 + chunk * 4);
+      q[j][nv * 4 + 0] = x.x * qscale;
+      q[j][nv * 4 + 1] = x.y * qscale;
+      q[j][nv * 4 + 2] = x.z * qscale;
+      q[j][nv * 4 + 3] = x.w * qscale;
     }
-  float mx[G], sum[G], o[G][DPL];
+  float mx[ROWS], sum[ROWS], o[ROWS][DPL];
 #pragma unroll
-  for (int j = 0; j < G; ++j) {
+  for (int j = 0; j < ROWS; ++j) {
     mx[j] = -INFINITY;
     sum[j] = 0.f;
 #pragma unroll
     for (int e = 0; e < DPL; ++e) o[j][e] = 0.f;
   }
-  const T* ck = reinterpret_cast<const T*>(cv.k);
-  const T* cvv = reinterpret_cast<const T*>(cv.v);
-  const int end = min(it.k1, m.pos + 1);
-  for (int base = it.k0; base < end; base += SLOTS) {
-    const int key = base + slot;
-    if (key < end) {  // uniform across the LPK lanes of a key, so DPP partners are active
-      const int64_t off = cache_offset(cv, layer, m.seq, hk, key) + chunk * DPL;
-      const T* vr = (cv.page_size ? v_row<true, T>(cv, layer, m.seq, hk, key) : cvv + off - chunk * DPL) + chunk * DPL;
-      float kx[DPL], vx[DPL];
+  const float* ck = reinterpret_cast<const float*>(cv.k);
+  const float* cvv = reinterpret_cast<const float*>(cv.v);
+  const int end = min(it.k1, pos[R - 1] + 1);  // positions ascend
+  // MASKED: the step may hold keys past the range or past a token's position
+  auto step = [&](int base, auto masked) __attribute__((always_inline)) {
+    constexpr bool MASKED = decltype(masked)::value;
+    float kx[U][DPL], vx[U][DPL];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int key = MASKED ? min(base + u * 16 + slot, end - 1) : base + u * 16 + slot;
+      const int64_t off = cache_offset(cv, layer, it.seq, hk, key);
+      const float* vr = cv.page_size ? v_row<true, float>(cv, layer, it.seq, hk, key) : cvv + off;
 #pragma unroll
       for (int nv = 0; nv < NV; ++nv) {
-        Store<T>::unpack(ld16(ck + off + nv * VEC), kx + nv * VEC);
-        Store<T>::unpack(ld16(vr + nv * VEC), vx + nv * VEC);
+        Store<float>::unpack(ld16(ck + off + nv * 64 + chunk * 4), kx[u] + nv * 4);
+        Store<float>::unpack(ld16(vr + nv * 64 + chunk * 4), vx[u] + nv * 4);
       }
-      float s[G];
+    }
 #pragma unroll
-      for (int j = 0; j < G; ++j) {
+    for (int j = 0; j < ROWS; ++j) {
+      float s[U], mn = mx[j];
+      bool seen[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
         float a = 0.f;
 #pragma unroll
-        for (int e = 0; e < DPL; ++e) a = fmaf(q[j][e], kx[e], a);
-        s[j] = group_sum<LPK>(a);
+        for (int e = 0; e < DPL; ++e) a = fmaf(q[j][e], kx[u][e], a);
+        s[u] = sum_lanes16(a);
+        seen[u] = !MASKED || base + u * 16 + slot < min(end, pos[j / G] + 1);
+        if (!seen[u]) s[u] = -INFINITY;
+        mn = fmaxf(mn, s[u]);
       }
+      const float ref = MASKED && mn == -INFINITY ? 0.f : mn;  // nothing seen yet: every weight 0
+      const float a = __builtin_amdgcn_exp2f(mx[j] - ref);      // v_exp_f32: -inf gives 0
+      mx[j] = mn;
+      sum[j] *= a;
 #pragma unroll
-      for (int j = 0; j < G; ++j) {
-        const float mn = fmaxf(mx[j], s[j]);
-        const float a = exp2f(mx[j] - mn);  // mx = -inf before the first key: a = 0
-        const float p = exp2f(s[j] - mn);
-        sum[j] = fmaf(sum[j], a, p);
+      for (int e = 0; e < DPL; ++e) o[j][e] *= a;
 #pragma unroll
-        for (int e = 0; e < DPL; ++e) o[j][e] = fmaf(o[j][e], a, p * vx[e]);
-        mx[j] = mn;
+      for (int u = 0; u < U; ++u) {
+        const float p = __builtin_amdgcn_exp2f(s[u] - ref);
+        sum[j] += p;
+#pragma unroll
+        for (int e = 0; e < DPL; ++e) o[j][e] = fmaf(p, seen[u] ? vx[u][e] : 0.f, o[j][e]);
+      }
+    }
+  };
+  int base = it.k0;
+  const int whole = min(end, pos[0] + 1);
+  for (; base + STEP <= whole; base += STEP) step(base, std::false_type{});
+  for (; base < end; base += STEP) step(base, std::true_type{});
+
+  // merge the four slots of each wave, then the waves
+#pragma unroll
+  for (int j = 0; j < ROWS; ++j) {
+    const float M = max_rows4(mx[j]);
+    const float f = mx[j] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mx[j] - M);
+    const float L = sum_rows4(sum[j] * f);
+#pragma unroll
+    for (int e = 0; e < DPL; ++e) o[j][e] = sum_rows4(o[j][e] * f);
+    if ((t & 63) < 16) {
+#pragma unroll
+      for (int nv = 0; nv < NV; ++nv)
+        *reinterpret_cast<float4*>(&s_o[w][j][nv * 64 + chunk * 4]) =
+            make_float4(o[j][nv * 4], o[j][nv * 4 + 1], o[j][nv * 4 + 2], o[j][nv * 4 + 3]);
+      if (chunk == 0) {
+        s_m[w][j] = M;
+        s_l[w][j] = L;
       }
     }
   }
-  // merge the SLOTS key slots of the block
-  if (chunk == 0) {
-#pragma unroll
-    for (int j = 0; j < G; ++j) { s_m[slot][j] = mx[j]; s_l[slot][j] = sum[j]; }
-  }
   __syncthreads();
-  if (t < G) {
+  for (int idx = t; idx < min(ROWS, it.n_rank * G) * (D / 4); idx += 256) {
+    const int j = idx / (D / 4), d = 4 * (idx % (D / 4));
     float M = -INFINITY;
-    for (int s2 = 0; s2 < SLOTS; ++s2) M = fmaxf(M, s_m[s2][t]);
+#pragma unroll
+    for (int w2 = 0; w2 < 4; ++w2) M = fmaxf(M, s_m[w2][j]);
     float L = 0.f;
-    if (M != -INFINITY)
-      for (int s2 = 0; s2 < SLOTS; ++s2)
-        if (s_m[s2][t] != -INFINITY) L += s_l[s2][t] * exp2f(s_m[s2][t] - M);
-    s_M[t] = M;
-    s_L[t] = L;
-  }
-  __syncthreads();
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-  for (int j = 0; j < G; ++j) {
-    const float M = s_M[j];
-    const float f = (M == -INFINITY || mx[j] == -INFINITY) ? 0.f : exp2f(mx[j] - M);
-#pragma unroll
-    for (int e = 0; e < DPL; ++e) s_o[slot][e][chunk] = o[j][e] * f;
-    __syncthreads();
-    for (int d = t; d < D; d += 256) {
-      const int c = d / DPL, e = d % DPL;
-      float acc = 0.f;
-      for (int s2 = 0; s2 < SLOTS; ++s2) acc += s_o[s2][e][c];
-      if (it.part < 0) {
-        const float L = s_L[j];
-        Store<T>::store1(out + ((int64_t)m.tok * Hq + hk * G + j) * D + d, L > 0.f ? acc / L : 0.f);
-      } else {
-        const int64_t row = ((int64_t)it.part * Hkv + hk) * part_stride_rows + j;
-        part_o[row * D + d] = acc;
-        if (d == 0) {
-          part_ml[row * 2 + 0] = s_M[j];
-          part_ml[row * 2 + 1] = s_L[j];
-        }
+    for (int w2 = 0; w2 < 4; ++w2) {
+      const float m = s_m[w2][j];
+      const float f = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - M);
+      const float4 x = *reinterpret_cast<const float4*>(&s_o[w2][j][d]);
+      L = fmaf(s_l[w2][j], f, L);
+      acc.x = fmaf(x.x, f, acc.x);
+      acc.y = fmaf(x.y, f, acc.y);
+      acc.z = fmaf(x.z, f, acc.z);
+      acc.w = fmaf(x.w, f, acc.w);
+    }
+    if (it.part < 0) {
+      const int tok = meta[it.rank0 + j / G].tok;
+      const bool any = L > 0.f;
+      *reinterpret_cast<float4*>(out + ((int64_t)tok * Hq + hk * G + j % G) * D + d) =
+          make_float4(any ? acc.x / L : 0.f, any ? acc.y / L : 0.f, any ? acc.z / L : 0.f, any ? acc.w / L : 0.f);
+    } else {
+      const int64_t row = ((int64_t)it.part * Hkv + hk) * part_stride_rows + j;
+      *reinterpret_cast<float4*>(part_o + row * D + d) = acc;
+      if (d == 0) {
+        part_ml[row * 2 + 0] = M;
+        part_ml[row * 2 + 1] = L;
       }
     }
-    __syncthreads();
   }
 }
 
@@ -289,33 +323,46 @@ __global__ void __launch_bounds__(256) combine_kernel(CombineArgs args, const To
   Store<T>::store1(dst + 3, acc.w);
 }
 
-int launch_attn_rows(int dtype, const AttnItem* items, int n_items, const TokenMeta* meta, const void* qws,
-                     int rows_ws, const CacheView& cv, int layer, int Hq, void* out, float* part_o,
-                     float* part_ml, int part_stride_rows, hipStream_t s, KTime tm) {
+int launch_attn_rows(const AttnItem* items, int n_items, const TokenMeta* meta, const void* qws, int rows_ws,
+                     const CacheView& cv, int layer, int Hq, void* out, float* part_o, float* part_ml,
+                     int part_stride_rows, int tokens, hipStream_t s, KTime tm) {
   if (n_items == 0) return 0;
   const int g = Hq / cv.n_kv_heads;
   dim3 grid(n_items, cv.n_kv_heads);
-#define AR(T, DD, GG)                                                                                       \
-  hipExtLaunchKernelGGL((attn_rows_kernel<T, DD, GG>), grid, dim3(256), 0, s, tm.start, tm.stop, 0, items, meta, (const T*)qws,      \
-                     rows_ws, cv, layer, Hq, (T*)out, part_o, part_ml, part_stride_rows)
-#define ARG(T, DD)                                                                                          \
-  switch (g) {                                                                                              \
-    case 1: AR(T, DD, 1); break;                                                                            \
-    case 2: AR(T, DD, 2); break;                                                                            \
-    case 4: AR(T, DD, 4); break;                                                                            \
-    case 8: AR(T, DD, 8); break;                                                                            \
-    case 16: AR(T, DD, 16); break;                                                                          \
-    default: return -1;                                                                                     \
+#define AR(DD, GG, RR)                                                                                       \
+  hipExtLaunchKernelGGL((attn_rows_kernel<DD, GG, RR>), grid, dim3(256), 0, s, tm.start, tm.stop, 0, items, meta, \
+                        (const float*)qws, rows_ws, cv, layer, Hq, (float*)out, part_o, part_ml, part_stride_rows)
+#define AR1(DD, GG) if (tokens == 1) AR(DD, GG, 1); else return -1
+#define AR2(DD, GG) if (tokens == 2) AR(DD, GG, 2); else AR1(DD, GG)
+#define AR4(DD, GG) if (tokens == 4) AR(DD, GG, 4); else AR2(DD, GG)
+  if (cv.head_dim == 64) {  // the instances attn_rows_tokens allows
+    switch (g) {
+      case 1: AR4(64, 1); break;
+      case 2: AR4(64, 2); break;
+      case 4: AR2(64, 4); break;
+      case 8: AR1(64, 8); break;
+      case 16: AR1(64, 16); break;
+      default: return -1;
+    }
+  } else {
+    switch (g) {
+      case 1: AR4(128, 1); break;
+      case 2: AR2(128, 2); break;
+      case 4: AR1(128, 4); break;
+      case 8: AR1(128, 8); break;
+      case 16: AR1(128, 16); break;
+      default: return -1;
+    }
   }
-  if (dtype == 0) { if (cv.head_dim == 64) { ARG(float, 64) } else { ARG(float, 128) } }
-  else { if (cv.head_dim == 64) { ARG(bf16_t, 64) } else { ARG(bf16_t, 128) } }
-#undef ARG
+#undef AR4
+#undef AR2
+#undef AR1
 #undef AR
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? 0 : (int)e;
 }
 
-int launch_combine(int dtype, const CombineArgs& args, const TokenMeta* meta, int Hq, int Hkv, int D,
+int launch_combine(const CombineArgs& args, const TokenMeta* meta, int Hq, int Hkv, int D,
                    const float* part_o, const float* part_ml, int part_stride_rows, void* out, hipStream_t s,
                    bool mfma_part, KTime tm) {
   if (args.n_items == 0) return 0;
@@ -326,15 +373,14 @@ int launch_combine(int dtype, const CombineArgs& args, const TokenMeta* meta, in
 #define CBK(T, DD, MP, PR)                                                                                  \
   hipExtLaunchKernelGGL((combine_kernel<T, DD, MP, PR>), grid, dim3(256), 0, s, tm.start, tm.stop, 0, args,   \
                         meta, Hq, Hkv, part_o, part_ml, part_stride_rows, (T*)out)
-#define CB(T, DD)                                                                                            \
+#define CB(DD)                                                                                               \
   do {                                                                                                       \
-    if (!mfma_part) CBK(T, DD, false, 16);                                                                   \
-    else if (pre == 4) CBK(T, DD, true, 4);                                                                  \
-    else if (pre == 16) CBK(T, DD, true, 16);                                                                \
-    else CBK(T, DD, true, 32);                                                                               \
+    if (!mfma_part) CBK(float, DD, false, 16);                                                               \
+    else if (pre == 4) CBK(bf16_t, DD, true, 4);                                                             \
+    else if (pre == 16) CBK(bf16_t, DD, true, 16);                                                           \
+    else CBK(bf16_t, DD, true, 32);                                                                          \
   } while (0)
-  if (dtype == 0) { if (D == 64) CB(float, 64); else CB(float, 128); }
-  else { if (D == 64) CB(bf16_t, 64); else CB(bf16_t, 128); }
+  if (D == 64) CB(64); else CB(128);
 #undef CB
 #undef CBK
   hipError_t e = hipGetLastError();

@@ -229,10 +229,19 @@ int launch_attn_mfma(const PrefillArgs& args, const TokenMeta* meta, const void*
                      int part_stride_rows, int nbuf, hipStream_t s, KTime tm = {}, FusedIn fin = {},
                      int wave_rows = 32);
 
-// VALU attention, one token (g query rows) per item; any dtype.
-int launch_attn_rows(int dtype, const AttnItem* items, int n_items, const TokenMeta* meta, const void* qws,
-                     int rows_ws, const CacheView& cv, int layer, int Hq, void* out, float* part_o,
-                     float* part_ml, int part_stride_rows, hipStream_t s, KTime tm = {});
+// fp32 attention: per item `tokens` (1, 2 or 4, up to attn_rows_tokens)
+// consecutive tokens of a sequence, g query rows each; part_stride_rows is
+// tokens * g.
+// At most 512 query elements: with 1024 the loads of a step have to be halved for
+// the registers (512 tokens over ~4K keys, g 8, D 64: 315 -> 399 us a call; g 4,
+// D 128: 253 -> 301; g 2, D 128 gains, 257 -> 211).
+inline int attn_rows_tokens(int g, int head_dim) {
+  const int r = 512 / (g * head_dim);
+  return r >= 4 ? 4 : r >= 2 ? 2 : 1;
+}
+int launch_attn_rows(const AttnItem* items, int n_items, const TokenMeta* meta, const void* qws, int rows_ws,
+                     const CacheView& cv, int layer, int Hq, void* out, float* part_o, float* part_ml,
+                     int part_stride_rows, int tokens, hipStream_t s, KTime tm = {});
 
 // Decode step: encode + store the new token and split-KV attention over the
 // cache.  q, k, v, out: [n][H][D] rows in the order of args.seq.  Grid
@@ -265,9 +274,9 @@ constexpr size_t kNoAllocPartBytes = (size_t)8 << 20;
 constexpr size_t kNoAllocScratchBytes = kNoAllocCountBytes + kNoAllocPartBytes;
 int noalloc_scratch(hipStream_t s, void** base);
 
-// Merge split partials into out: part_o fp32 rows, or (mfma_part) bf16 in the
-// accumulator order of the MFMA prefill kernel.
-int launch_combine(int dtype, const CombineArgs& args, const TokenMeta* meta, int Hq, int Hkv, int D,
+// Merge split partials into out: part_o and out fp32 rows, or (mfma_part) both
+// bf16, part_o in the accumulator order of the MFMA prefill kernel.
+int launch_combine(const CombineArgs& args, const TokenMeta* meta, int Hq, int Hkv, int D,
                    const float* part_o, const float* part_ml, int part_stride_rows, void* out, hipStream_t s,
                    bool mfma_part = false, KTime tm = {});
 

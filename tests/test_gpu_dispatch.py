@@ -62,3 +62,16 @@ def test_prefill_tile_addresses(d, g, page, alias, n_fresh):
     w = synth.custom(synth.Shape(1, 2 * g, 2, d, 1e6, "bf16"), 7, lens, [[i] for i in range(len(lens))], n_fresh, 1,
                      page_size=page)
     parity.run_pipeline(w, [0], 1, list(range(len(lens))), alias=alias)
+
+
+@pytest.mark.parametrize("d,g", [(64, 1), (64, 2), (64, 4), (64, 8), (64, 16), (128, 1), (128, 2), (128, 4),
+                                 (128, 8), (128, 16)])
+@pytest.mark.parametrize("page,alias", [(0, False), (16, True)])
+@pytest.mark.parametrize("n_fresh,lens", [(1, [1, 127, 128, 700]), (7, [1, 57, 63, 121, 122, 700]),
+                                          (131, [1, 900, 2500, 2600])])
+def test_fp32_prefill_row_blocks(d, g, page, alias, n_fresh, lens):
+    """The fp32 prefill over 1, 2 and 4 tokens a block (few and many blocks a call), blocks of fewer
+    tokens than that, key splits of one and of several tiles, contexts around multiples of a step."""
+    w = synth.custom(synth.Shape(1, 2 * g, 2, d, 1e4, "f32"), 9, lens, [[i] for i in range(len(lens))], n_fresh, 1,
+                     page_size=page)
+    parity.run_pipeline(w, [0], 1, list(range(len(lens))), alias=alias)

@@ -342,8 +342,6 @@ fcg_status grow(void** p, size_t* have, size_t need, const char* what) {
   return FCG_OK;
 }
 
-// After a planner check: map the new pages, and prepare the device copies of
-// the touched page-table rows (appended to the blob).
 // The device row of seq: its page row, then its value-alias row.
 size_t stage_row(const fcg_cache* c, int32_t seq, Blob* blob) {
   const size_t nlp = c->plan.n_logical_pages();
@@ -353,12 +351,17 @@ size_t stage_row(const fcg_cache* c, int32_t seq, Blob* blob) {
   return blob->add(row.data(), row.size() * sizeof(int32_t));
 }
 
+// After a planner check: map the new pages, and prepare the device copies of
+// the page-table rows that change (appended to the blob): those of the new
+// pages' sequences and of `seqs`.
 void stage_pages(fcg_cache* c, const std::vector<std::pair<int32_t, int32_t>>& new_pages, Blob* blob,
-                 std::vector<std::pair<int32_t, size_t>>* rows) {
+                 std::vector<std::pair<int32_t, size_t>>* rows, std::vector<int32_t> seqs = {}) {
   c->plan.map_pages(new_pages);
-  int32_t last = -1;  // new pages come in (sequence, logical page) order
-  for (auto& sl : new_pages)
-    if (sl.first != last) rows->push_back({last = sl.first, stage_row(c, sl.first, blob)});
+  for (auto& sl : new_pages)  // in (sequence, logical page) order
+    if (seqs.empty() || seqs.back() != sl.first) seqs.push_back(sl.first);
+  if (!std::is_sorted(seqs.begin(), seqs.end())) std::sort(seqs.begin(), seqs.end());
+  seqs.erase(std::unique(seqs.begin(), seqs.end()), seqs.end());
+  for (int32_t s : seqs) rows->push_back({s, stage_row(c, s, blob)});
 }
 
 // Upload a plan: the staged page rows (at the front of the blob, in the order
@@ -878,11 +881,12 @@ fcg_status fcg_graft(fcg_cache* c, const fcg_lib* lib, int32_t n_items, const in
     return fail(FCG_EINVAL, "a cache with FCG_ALIAS_V grafts from one library only");
   for (auto& sp : spans)
     if (lib->segs[sp.seg].tok_off < 0) return fail(FCG_ESTATE, "segment is not in device memory (fcg_lib_reload)");
+  std::vector<int32_t> realiased;  // sequences of which a page mapped before now reads its values from the library
   if (c->plan.alias_v()) {
     c->alias_lib = lib;
     if (c->alias_segs.empty()) c->alias_segs.resize(c->n_seqs);
     for (auto& sp : spans) {
-      c->plan.alias_pages(sp.seq, sp.dst, sp.len, lib->segs[sp.seg].tok_off);
+      if (c->plan.alias_pages(sp.seq, sp.dst, sp.len, lib->segs[sp.seg].tok_off)) realiased.push_back(sp.seq);
       ++lib->segs[sp.seg].pins;  // its values may now be read in place: no offload until the sequence is reset
       c->alias_segs[sp.seq].push_back(sp.seg);
     }
@@ -896,9 +900,9 @@ fcg_status fcg_graft(fcg_cache* c, const fcg_lib* lib, int32_t n_items, const in
   hipStream_t s = (hipStream_t)stream;
   Blob blob;
   std::vector<std::pair<int32_t, size_t>> rows;
-  stage_pages(c, new_pages, &blob, &rows);
+  stage_pages(c, new_pages, &blob, &rows, std::move(realiased));
   // up to kGraftArgItems segments in kGraftArgRuns runs go by value, and
-  // nothing is uploaded unless the call maps pages; longer lists go through the
+  // nothing is uploaded unless page rows change; longer lists go through the
   // staging ring
   int64_t n_runs = 0;
   for (auto& sp : spans) n_runs += (sp.len + kGraftChunk - 1) / kGraftChunk;

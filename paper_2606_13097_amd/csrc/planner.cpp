@@ -211,10 +211,14 @@ void Planner::mark_all_layers(int32_t seq, int32_t dst, int32_t len) {
   }
 }
 
-void Planner::alias_pages(int32_t seq, int32_t dst, int32_t len, int64_t lib_tok0) {
-  if (!AV_) return;
-  for (int32_t lp = (dst + P_ - 1) / P_; (lp + 1) * P_ <= dst + len; ++lp)
+bool Planner::alias_pages(int32_t seq, int32_t dst, int32_t len, int64_t lib_tok0) {
+  if (!AV_) return false;
+  bool mapped = false;
+  for (int32_t lp = (dst + P_ - 1) / P_; (lp + 1) * P_ <= dst + len; ++lp) {
     valias_[(size_t)seq * NLP_ + lp] = (int32_t)(lib_tok0 + (int64_t)lp * P_ - dst);
+    mapped |= page_table_[(size_t)seq * NLP_ + lp] >= 0;
+  }
+  return mapped;
 }
 
 void Planner::reset(int32_t seq) {

@@ -59,8 +59,10 @@ class Planner {
   void mark_all_layers(int32_t seq, int32_t dst, int32_t len);
   // graft of len tokens at dst whose first token is library token lib_tok0:
   // with alias_v, the logical pages inside [dst, dst + len) map their values
-  // onto the library
-  void alias_pages(int32_t seq, int32_t dst, int32_t len, int64_t lib_tok0);
+  // onto the library.  Called before map_pages; true if one of them is mapped
+  // already (a cut left it mapped and empty), so that the sequence's device row
+  // changes although the call need not map a page of it
+  bool alias_pages(int32_t seq, int32_t dst, int32_t len, int64_t lib_tok0);
   void mark(int32_t seq, int32_t layer, int32_t pos);
   void reset(int32_t seq);
   // keep [0, pos) in every layer (the caller checked the range); a split

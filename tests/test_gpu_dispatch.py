@@ -75,3 +75,26 @@ def test_fp32_prefill_row_blocks(d, g, page, alias, n_fresh, lens):
     w = synth.custom(synth.Shape(1, 2 * g, 2, d, 1e4, "f32"), 9, lens, [[i] for i in range(len(lens))], n_fresh, 1,
                      page_size=page)
     parity.run_pipeline(w, [0], 1, list(range(len(lens))), alias=alias)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n_kept", [2, 40])
+def test_graft_aliases_a_page_a_cut_left_mapped(dtype, n_kept, monkeypatch):
+    """A segment grafted behind a gap and cut away again leaves the cut page mapped and empty; a
+    segment that then covers the page reads its values from the library though the call maps no new
+    page of that sequence (up to 32 segments, by value, and more, uploaded)."""
+    from paper_2606_13097_amd import fcg, runner
+    plain = runner.GpuSetup.graft
+
+    def graft(self):
+        for s in range(n_kept):
+            fcg.fcg_graft(self.cache, self.lib, [s], [0], [5])
+            fcg.fcg_cache_truncate(self.cache, s, 5)
+        plain(self)
+
+    monkeypatch.setattr(runner.GpuSetup, "graft", graft)
+    # no fresh tokens: a prefill that maps a page would bring the row up to date
+    check = parity.check_attn
+    monkeypatch.setattr(parity, "check_attn", lambda got, *a: check(got, *a) if got.size else None)
+    w = synth.custom(synth.Shape(2, 4, 2, 64, 1e4, dtype), 11, [8, 16, 37], [[1]] * n_kept + [[2]], 0, 3, page_size=16)
+    parity.run_pipeline(w, [1], 3, [0, n_kept - 1, n_kept], alias=True)

@@ -974,9 +974,10 @@ fcg_status run_attention(fcg_cache* c, int32_t layer, const std::vector<TokenMet
   // positions given at consecutive caller indices (a patch span following its
   // context) run as one fused kernel: it encodes the queries itself, reads the
   // fresh keys and values from the caller's arrays and stores them into the
-  // cache.  Other calls encode and append first (rope_append).
+  // cache.  Other calls encode and append first (rope_append), as do those whose
+  // k or v is not 16-byte aligned: the fused kernel brings these rows in by LDS DMA.
   std::vector<std::pair<int32_t, int32_t>> seq_first(d.dtype == FCG_BF16 ? n : 0);  // per rank: (f0, ftok0)
-  bool fused = mfma;
+  bool fused = mfma && (((uintptr_t)k | (uintptr_t)v) & 15) == 0;
   for (int r0 = 0; fused && r0 < n;) {
     int r1 = r0;
     while (r1 < n && meta[r1].seq == meta[r0].seq) {

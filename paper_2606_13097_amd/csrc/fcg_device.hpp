@@ -58,6 +58,12 @@ template <> struct Store<bf16_t> {
 };
 
 __device__ __forceinline__ uint4 ld16(const void* p) { return *reinterpret_cast<const uint4*>(p); }
+// the same from any address
+__device__ __forceinline__ uint4 ld16_any(const void* p) {
+  uint4 x;
+  __builtin_memcpy(&x, p, 16);
+  return x;
+}
 
 // 16-byte load with the nontemporal hint (global_load ... nt): for data read
 // once, which then does not displace reused lines from the caches
@@ -112,6 +118,8 @@ __device__ __forceinline__ uint32_t lds_addr(const void* p) {
 // wave-uniform).  Inline assembly, so that the compiler's own wait
 // bookkeeping, which cannot tell the ring's buffers apart, adds no
 // vmcnt(0) before each tile's LDS reads; the waits are explicit (wait_vm).
+// g is 16-byte aligned: rows of caches and tables are, a caller's tensors need
+// not be (ordinary loads take any address).
 __device__ __forceinline__ void dma16(const void* g, uint32_t lds) {
   asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "{m0}"(lds) : "memory");
 }

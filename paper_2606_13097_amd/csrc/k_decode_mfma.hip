@@ -194,18 +194,25 @@ __global__ void __launch_bounds__(256) decode_mfma_kernel(DecodeArgs args, const
   // tiles.  Each wave fetches its own copy, so none waits for another.
   constexpr int PRE = NB - 1;
   Entry nx = entry(0);
-  const char* stage = ring + (NB - 1) * TILE;
+  char* stage = ring + (NB - 1) * TILE;
   const uint32_t stage_lds = ring_lds + (NB - 1) * TILE;
   {
+    const char* qr = reinterpret_cast<const char*>(q + ((int64_t)i * Hq + hk * G) * D);
     const char* kr = reinterpret_cast<const char*>(k + ((int64_t)i * Hkv + hk) * D);
     const char* vr = reinterpret_cast<const char*>(v + ((int64_t)i * Hkv + hk) * D);
     const char* cr = reinterpret_cast<const char*>(rope + (int64_t)pos * HALF);
     const char* src = l < NC ? kr + l * 16 : l < 2 * NC ? vr + (l - NC) * 16 : cr + min(l - 2 * NC, NCS - 1) * 16;
-    dma16(src, stage_lds);
+    if (__builtin_expect((((uintptr_t)q | (uintptr_t)k | (uintptr_t)v) & 15) == 0, 1)) {
+      dma16(src, stage_lds);
 #pragma unroll
-    for (int j = 0; j < QI; ++j)
-      dma16s(q + ((int64_t)i * Hq + hk * G) * D, (uint32_t)min(j * 64 + l, G * NC - 1) * 16,
-             stage_lds + (1 + j) * 1024);
+      for (int j = 0; j < QI; ++j)
+        dma16s(qr, (uint32_t)min(j * 64 + l, G * NC - 1) * 16, stage_lds + (1 + j) * 1024);
+    } else {  // a caller's rows may start at any element: ordinary loads there, LDS DMA takes whole 16-byte words
+      st16(stage + l * 16, ld16_any(src));
+#pragma unroll 1
+      for (int j = 0; j < QI; ++j)
+        st16(stage + (1 + j) * 1024 + l * 16, ld16_any(qr + min(j * 64 + l, G * NC - 1) * 16));
+    }
   }
 #pragma unroll 1  // one copy of the code: every instruction of a short launch is fetched for it
   for (int u = 0; u < min(n, PRE); ++u) {

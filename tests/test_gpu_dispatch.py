@@ -98,3 +98,31 @@ def test_graft_aliases_a_page_a_cut_left_mapped(dtype, n_kept, monkeypatch):
     monkeypatch.setattr(parity, "check_attn", lambda got, *a: check(got, *a) if got.size else None)
     w = synth.custom(synth.Shape(2, 4, 2, 64, 1e4, dtype), 11, [8, 16, 37], [[1]] * n_kept + [[2]], 0, 3, page_size=16)
     parity.run_pipeline(w, [1], 3, [0, n_kept - 1, n_kept], alias=True)
+
+
+@pytest.mark.parametrize("dtype,d,g,page,shift", [("bf16", 128, 4, 0, 1), ("bf16", 128, 4, 0, 4), ("bf16", 64, 1, 16, 1),
+                                                  ("bf16", 128, 16, 16, 2), ("f32", 64, 2, 0, 1)])
+def test_tensors_at_any_element(dtype, d, g, page, shift, monkeypatch):
+    """q, k, v and out that start at any element of a buffer (a multiple of 16 bytes selects the loads
+    straight into LDS, others the ordinary ones)."""
+    from paper_2606_13097_amd import fcg
+
+    def moved(t):
+        buf = torch.empty(t.numel() + shift, dtype=t.dtype, device=t.device)
+        buf[shift:].copy_(t.reshape(-1))
+        return buf[shift:].view(t.shape)
+
+    def shifted(fn, n_lead):
+        def call(*args):
+            q, k, v, out = (moved(t) for t in args[n_lead:])
+            assert q.data_ptr() % 16
+            res = fn(*args[:n_lead], q, k, v, out)
+            args[-1].copy_(out)
+            return res
+        return call
+
+    monkeypatch.setattr(fcg, "fcg_patch_prefill", shifted(fcg.fcg_patch_prefill, 4))
+    plain_decode = shifted(fcg.fcg_decode, 3)
+    monkeypatch.setattr(fcg, "fcg_decode", lambda *a: plain_decode(*a[:7]))   # the runner passes a stream, None
+    w = synth.custom(synth.Shape(1, 2 * g, 2, d, 1e4, dtype), 13, [70, 800], [[0], [1]], 9, 3, page_size=page)
+    parity.run_pipeline(w, [0], 3, [0, 1])

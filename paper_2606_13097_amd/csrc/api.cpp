@@ -1161,58 +1161,6 @@ fcg_status run_attention(fcg_cache* c, int32_t layer, const std::vector<TokenMet
   return upload_plan ? c->ring.retire(off, blob.bytes.size(), s) : FCG_OK;
 }
 
-// Split plan of one decode call: split length in keys and the largest number
-// of partial slots any launch group needs.
-struct DecodePlan {
-  int64_t split_keys = 0;
-  int max_slots = 0;
-  int ring = 4;  // 16-key tiles of a wave's LDS ring (bf16)
-  size_t part_o = 0, part_ml = 0;  // floats of the partial outputs and of the (max, sum) pairs
-};
-
-DecodePlan plan_decode(const fcg_model_desc& d, int32_t n, const std::vector<int32_t>& pos) {
-  const int g = d.n_q_heads / d.n_kv_heads;
-  int64_t total = 0;
-  int32_t pmax = 0;
-  for (int32_t i = 0; i < n; ++i) {
-    total += pos[i] + 1;
-    pmax = std::max(pmax, pos[i]);
-  }
-  // split length: the smallest (from 64 keys up) whose blocks fit in one
-  // wave of the grid -- one block per compute unit while that leaves at most
-  // 256 keys per block (fewer partials for the merge in each (sequence, kv
-  // head)'s last block), two per compute unit for more keys (shorter key
-  // loops) -- rounded up to whole 64-key chunks; at most 256 splits per
-  // sequence, and at most 32 when planning two blocks per compute unit: past
-  // that the last block's fold of the partials costs more than the shorter
-  // key loops save (16.7K-token context at batch 1: 53 splits 20.4 us per
-  // call, 30 splits 19.1 us)
-  const bool two_per_cu = total * d.n_kv_heads > 256 * 256;
-  const int64_t target_blocks = two_per_cu ? 512 : 256;
-  const int64_t max_splits = two_per_cu ? 32 : 256;
-  int64_t sk = std::max<int64_t>(64, (total * d.n_kv_heads + target_blocks - 1) / target_blocks);
-  sk = std::max<int64_t>(sk, (pmax + 1 + max_splits - 1) / max_splits);
-  for (;;) {
-    int64_t blocks = 0;
-    for (int32_t i = 0; i < n; ++i) blocks += (pos[i] + sk) / sk;
-    if (blocks * d.n_kv_heads <= target_blocks || blocks <= n) break;
-    sk += (sk + 31) / 32;  // about 3% longer
-  }
-  sk = (sk + 63) / 64 * 64;
-  DecodePlan p;
-  p.split_keys = sk;
-  p.ring = two_per_cu ? 2 : 4;
-  // partial slots: one per split of every multi-split sequence of a launch group
-  for (int32_t i0 = 0; i0 < n; i0 += kMaxDecodeSeqs) {
-    int slots = 0;
-    for (int32_t i = i0; i < std::min<int32_t>(n, i0 + kMaxDecodeSeqs); ++i) slots += (int)((pos[i] + sk) / sk);
-    p.max_slots = std::max(p.max_slots, slots);
-  }
-  p.part_o = (size_t)p.max_slots * d.n_kv_heads * g * d.head_dim;
-  p.part_ml = (size_t)p.max_slots * d.n_kv_heads * g * 2;
-  return p;
-}
-
 // One decode launch per group of up to kMaxDecodeSeqs sequences; the launch
 // merges the splits of each sequence itself and takes its plan by value
 // (pages the step maps included), so a decode step uploads nothing.
@@ -1277,7 +1225,7 @@ std::vector<int32_t> decode_new_pages(const fcg_cache* c, int32_t n, const int32
 fcg_status run_decode(fcg_cache* c, int32_t layer, int32_t n, const int32_t* seqs, const std::vector<int32_t>& pos,
                       const void* q, const void* k, const void* v, void* out,
                       const std::vector<std::pair<int32_t, int32_t>>& new_pages, hipStream_t s) {
-  const DecodePlan plan = plan_decode(c->desc, n, pos);
+  const DecodePlan plan = plan_decode(c->desc, pos, kMaxDecodeSeqs);
   if (fcg_status st = grow((void**)&c->dpart, &c->dpart_bytes, (plan.part_o + plan.part_ml) * sizeof(float),
                            "decode partials"))
     return st;
@@ -1353,7 +1301,7 @@ fcg_status fcg_decode_noalloc(fcg_cache* c, int32_t layer, int32_t n_seqs, const
   std::string msg;
   if (fcg_status st = c->plan.check_decode(layer, n_seqs, seqs, &pos, &new_pages, &msg)) return fail(st, msg);
   if (n_seqs == 0) return FCG_OK;
-  const DecodePlan plan = plan_decode(c->desc, n_seqs, pos);
+  const DecodePlan plan = plan_decode(c->desc, pos, kMaxDecodeSeqs);
   const size_t need = (plan.part_o + plan.part_ml) * sizeof(float);
   if (need > kNoAllocPartBytes)
     return fail(FCG_ENOMEM, "this step needs " + std::to_string(need) + " bytes of split partials; the static scratch of "

@@ -384,11 +384,11 @@ __global__ void __launch_bounds__(256) decode_mfma_kernel(DecodeArgs args, const
                                    reinterpret_cast<float*>(s_ring), s_mt, s_lt, &s_last);
 }
 
-// ring: 4 (128 KB of LDS at D 128, one block per CU) where the plan gives every
-// CU at most one short split: all of it is requested at once.  2 (two blocks per
-// CU) for more keys; those launches also read with the nontemporal hint, the
-// keys always and the values unless the tasks share them in the library: whole
-// rows read that way arrive at 6.9 TB/s against 6.2 (measured on the kernel, with
+// ring: 4 where every CU has at most one block of at most 256 keys (plan_decode):
+// all of a wave's tiles are requested at once.  2 (two blocks per CU) otherwise; those
+// launches also read with the nontemporal hint, the keys
+// always and the values unless the tasks share them in the library: whole rows
+// read that way arrive at 6.9 TB/s against 6.2 (measured on the kernel, with
 // against without: 796 MB 2001 / 2184 us, 369 MB 506 / 553, 131 MB 439 / 460, 44
 // MB 425 / 432 per pass; 17.5 MB 1218 / 1201, so not there; shared values
 // 1125 / 1097).

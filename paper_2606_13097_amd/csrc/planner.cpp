@@ -263,4 +263,64 @@ void Planner::truncate(int32_t seq, int32_t pos, std::vector<Unalias>* unalias) 
     }
 }
 
+DecodePlan plan_decode(const fcg_model_desc& d, const std::vector<int32_t>& pos, int32_t max_seqs) {
+  const int32_t n = (int32_t)pos.size();
+  const int g = d.n_q_heads / d.n_kv_heads;
+  int64_t total = 0;
+  int32_t pmax = 0;
+  for (int32_t i = 0; i < n; ++i) {
+    total += pos[i] + 1;
+    pmax = std::max(pmax, pos[i]);
+  }
+  // split length: the smallest (from 64 keys up) whose blocks fit in one
+  // wave of the grid -- one block per compute unit while that leaves at most
+  // 256 keys per block (fewer partials for the merge in each (sequence, kv
+  // head)'s last block), two per compute unit for more keys (shorter key
+  // loops) -- rounded up to whole 64-key chunks; at most 256 splits per
+  // sequence, and at most 32 when planning two blocks per compute unit: past
+  // that the last block's fold of the partials costs more than the shorter
+  // key loops save (16.7K-token context at batch 1: 53 splits 20.4 us per
+  // call, 30 splits 19.1 us)
+  const bool two_per_cu = total * d.n_kv_heads > 256 * 256;
+  const int64_t target_blocks = two_per_cu ? 512 : 256;
+  const int64_t max_splits = two_per_cu ? 32 : 256;
+  int64_t sk = std::max<int64_t>(64, (total * d.n_kv_heads + target_blocks - 1) / target_blocks);
+  sk = std::max<int64_t>(sk, (pmax + 1 + max_splits - 1) / max_splits);
+  for (;;) {
+    int64_t blocks = 0;
+    for (int32_t i = 0; i < n; ++i) blocks += (pos[i] + sk) / sk;
+    if (blocks * d.n_kv_heads <= target_blocks || blocks <= n) break;
+    sk += (sk + 31) / 32;  // about 3% longer
+  }
+  sk = (sk + 63) / 64 * 64;
+  DecodePlan p;
+  p.split_keys = sk;
+  // partial slots: one per split of every multi-split sequence of a launch group
+  int64_t grid = 0;  // the largest launch's blocks, the empty ones of its shorter sequences included
+  for (int32_t i0 = 0; i0 < n; i0 += max_seqs) {
+    const int32_t i1 = std::min<int32_t>(n, i0 + max_seqs);
+    int slots = 0;
+    int64_t longest = 0;
+    for (int32_t i = i0; i < i1; ++i) {
+      slots += (int)((pos[i] + sk) / sk);
+      longest = std::max(longest, (pos[i] + sk) / sk);
+    }
+    p.max_slots = std::max(p.max_slots, slots);
+    grid = std::max(grid, longest * (i1 - i0) * d.n_kv_heads);
+  }
+  // Ring of four tiles a wave (128 KB of LDS at D 128, so one block per compute
+  // unit) when planning one block per unit, and only while the whole grid fits
+  // so: empty blocks need the LDS too, and a larger grid ran in rounds (kernel us
+  // of a 32-layer pass, 8 kv heads, D 128, ring of two against four: 64 x 100
+  // tokens 8.3 / 11.2, 64 x 30 5.1 / 7.7, four tasks of 200-3000 tokens 11.7 /
+  // 15.3).  Within it the two rings are alike up to run noise but for one 64-key
+  // split per unit (1 x 2000: 8.0 / 7.5) and paged caches that stay in the
+  // last-level cache, which the nontemporal reads of the ring of two bypass
+  // (32 x 250, four layers: 9.9 / 8.7).
+  p.ring = !two_per_cu && grid <= 256 ? 4 : 2;
+  p.part_o = (size_t)p.max_slots * d.n_kv_heads * g * d.head_dim;
+  p.part_ml = (size_t)p.max_slots * d.n_kv_heads * g * 2;
+  return p;
+}
+
 }  // namespace fcg

@@ -103,4 +103,15 @@ class Planner {
   void return_page(int32_t p);
 };
 
+// Split plan of one decode call: split length in keys and the largest number
+// of partial slots any launch group needs.
+struct DecodePlan {
+  int64_t split_keys = 0;
+  int max_slots = 0;
+  int ring = 4;  // 16-key tiles of a wave's LDS ring (bf16)
+  size_t part_o = 0, part_ml = 0;  // floats of the partial outputs and of the (max, sum) pairs
+};
+// pos: the position of each sequence's new token; launches take up to max_seqs sequences.
+DecodePlan plan_decode(const fcg_model_desc& d, const std::vector<int32_t>& pos, int32_t max_seqs);
+
 }  // namespace fcg

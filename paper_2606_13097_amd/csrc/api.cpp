@@ -1194,10 +1194,10 @@ fcg_status launch_decode_groups(fcg_cache* c, int32_t layer, int32_t n, const in
     // bf16: matrix-core kernel; fp32: the vector-ALU kernel
     int rc = d.dtype == FCG_BF16
                  ? launch_decode_mfma(a, (const char*)q + qoff, (const char*)k + koff, (const char*)v + koff, cv,
-                                      layer, c->d_rope, d.n_q_heads, (char*)out + qoff, part_o, part_ml, count, plan.ring, s,
-                                      KTime{e0, e1})
-                 : launch_decode(d.dtype, a, (const char*)q + qoff, (const char*)k + koff, (const char*)v + koff, cv,
-                                 layer, c->d_rope, d.n_q_heads, (char*)out + qoff, part_o, part_ml, count, s,
+                                      layer, c->d_rope, d.n_q_heads, (char*)out + qoff, part_o, part_ml, count,
+                                      plan.ring, s, KTime{e0, e1})
+                 : launch_decode(a, (const char*)q + qoff, (const char*)k + koff, (const char*)v + koff, cv, layer,
+                                 c->d_rope, d.n_q_heads, (char*)out + qoff, part_o, part_ml, count, s,
                                  KTime{e0, e1});
     if (rc) return hip_fail((hipError_t)rc, "decode launch");
     if (timing) {

@@ -81,7 +81,6 @@ __device__ __forceinline__ void merge_splits(const DecodeArgs& args, int i, int 
                                              int Hq, T* __restrict__ out, const float* part_o,
                                              const float* part_ml, int* count, float* s_buf, float* s_mt,
                                              float* s_lt, int* s_flag) {
-  constexpr bool BF = sizeof(T) == 2;
   const int t = threadIdx.x;
   // Ordering of the cross-block merge, stated in the hardware's terms (the
   // atomics are relaxed: release/acquire at agent scope writes back and

@@ -1,5 +1,6 @@
-// One decode step at one layer for a batch of sequences (Sec. 4.2, Eq. 6:
-// decoding over the reused, grafted KV states).
+// One decode step at one layer for a batch of sequences, fp32 caches (Sec. 4.2,
+// Eq. 6: decoding over the reused, grafted KV states; bf16 caches take the
+// matrix-core kernel).
 //
 // Per sequence i the new token sits at position pos_i = its current length.
 // Block (split s, sequence i, kv head h) attends the token's g query heads
@@ -36,26 +37,12 @@ __device__ __forceinline__ float dpp_f(float x) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, false));
 }
 
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-
-// a.lo * b.lo + a.hi * b.hi + c over bf16 pairs (v_dot2c_f32_bf16, fp32 accumulate)
-__device__ __forceinline__ float dot2_bf16(uint32_t a, uint32_t b, float c) {
-  return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, a), __builtin_bit_cast(bf16x2_t, b), c, false);
-}
-
 template <int LPK>
 __device__ __forceinline__ float lanes_sum(float x) {
   if (LPK >= 2) x += dpp_f<0xB1>(x);   // quad_perm [1,0,3,2]
   if (LPK >= 4) x += dpp_f<0x4E>(x);   // quad_perm [2,3,0,1]
   if (LPK >= 8) x += dpp_f<0x141>(x);  // row_half_mirror
   if (LPK >= 16) x += dpp_f<0x140>(x); // row_mirror
-  return x;
-}
-
-template <int W>  // sum over the lanes of a wave that are W, 2W, ... apart
-__device__ __forceinline__ float lanes_sum_stride(float x) {
-#pragma unroll
-  for (int o = W; o < 64; o *= 2) x += __shfl_xor(x, o);
   return x;
 }
 
@@ -74,8 +61,7 @@ __global__ void __launch_bounds__(256) decode_kernel(DecodeArgs args, const T* _
   constexpr int CK = U * SLOTS;    // keys per chunk
   constexpr int HALF = D / 2;
   constexpr int JB = G < 4 ? G : 4;  // query heads per LDS merge round
-  constexpr bool BF = sizeof(T) == 2;  // bf16: scores with v_dot2 on packed pairs
-  constexpr int NW = DPL / 2;          // packed pairs per lane
+  static_assert(sizeof(T) == 4, "fp32 caches");
   __shared__ float s_cos[HALF], s_sin[HALF];
   __shared__ float s_m[SLOTS][G], s_l[SLOTS][G];
   // slot outputs [SLOTS][JB][D]; in the cross-split merge, the split
@@ -180,36 +166,19 @@ __global__ void __launch_bounds__(256) decode_kernel(DecodeArgs args, const T* _
     }
   };
   const float qscale = 1.4426950408889634f / sqrtf((float)D);
-  // encoded queries: fp32 pre-scaled (fp32 storage), or the rounded bf16
-  // values packed in pairs, the score scaled after the dot product
-  float qf[G][DPL];
-  uint32_t qp[G][NW];
+  float qf[G][DPL];  // encoded queries, pre-scaled
 #pragma unroll
   for (int j = 0; j < G; ++j) {
     encode(qa[j], qb[j], qf[j]);
 #pragma unroll
-    for (int e = 0; e < NW; ++e)
-      qp[j][e] = (__float_as_uint(qf[j][2 * e]) >> 16) | (__float_as_uint(qf[j][2 * e + 1]) & 0xFFFF0000u);
-#pragma unroll
     for (int e = 0; e < DPL; ++e) qf[j][e] *= qscale;
   }
   // scaled score of query head j against this lane's dims of a key
-  auto score = [&](int j, const uint4 (&kw)[NV], const float* kx) -> float {
+  auto score = [&](int j, const float* kx) -> float {
     float a = 0.f;
-    if constexpr (BF) {
 #pragma unroll
-      for (int nv = 0; nv < NV; ++nv) {
-        a = dot2_bf16(qp[j][4 * nv + 0], kw[nv].x, a);
-        a = dot2_bf16(qp[j][4 * nv + 1], kw[nv].y, a);
-        a = dot2_bf16(qp[j][4 * nv + 2], kw[nv].z, a);
-        a = dot2_bf16(qp[j][4 * nv + 3], kw[nv].w, a);
-      }
-      return lanes_sum<LPK>(a) * qscale;
-    } else {
-#pragma unroll
-      for (int e = 0; e < DPL; ++e) a = fmaf(qf[j][e], kx[e], a);
-      return lanes_sum<LPK>(a);
-    }
+    for (int e = 0; e < DPL; ++e) a = fmaf(qf[j][e], kx[e], a);
+    return lanes_sum<LPK>(a);
   };
 
   float mx[G], sm[G], o[G][DPL];
@@ -228,13 +197,11 @@ __global__ void __launch_bounds__(256) decode_kernel(DecodeArgs args, const T* _
     for (int u = 0; u < U; ++u) {
       const bool ok = b + u * SLOTS + slot < kend;
       float kx[DPL];
-      if constexpr (!BF) {
 #pragma unroll
-        for (int nv = 0; nv < NV; ++nv) Store<T>::unpack(kk[u][nv], kx + nv * VEC);
-      }
+      for (int nv = 0; nv < NV; ++nv) Store<T>::unpack(kk[u][nv], kx + nv * VEC);
 #pragma unroll
       for (int j = 0; j < G; ++j) {
-        const float a = score(j, kk[u], kx);
+        const float a = score(j, kx);
         s[u][j] = ok ? a : -INFINITY;
       }
     }
@@ -287,12 +254,9 @@ __global__ void __launch_bounds__(256) decode_kernel(DecodeArgs args, const T* _
       st16(kdst + nv * VEC, Store<T>::pack(kn + nv * VEC));
       st16(vdst + nv * VEC, nvv[nv]);
     }
-    uint4 knw[NV];  // the rounded key, packed again (exact: bf16 values)
-#pragma unroll
-    for (int nv = 0; nv < NV; ++nv) knw[nv] = Store<T>::pack(kn + nv * VEC);
 #pragma unroll
     for (int j = 0; j < G; ++j) {
-      const float a = score(j, knw, kn);
+      const float a = score(j, kn);
       const float mn = fmaxf(mx[j], a);
       const float f = __builtin_amdgcn_exp2f(mx[j] - mn), p = __builtin_amdgcn_exp2f(a - mn);
       sm[j] = fmaf(sm[j], f, p);
@@ -358,35 +322,35 @@ __global__ void __launch_bounds__(256) decode_kernel(DecodeArgs args, const T* _
   if (nsplit == 1) return;
   static_assert(merge_lanes<T, D, G>() <= SLOTS && 256 * 16 / (int)sizeof(T) <= NBUF, "the merge uses the slot tables");
   merge_splits<T, D, G>(args, i, hk, slot0, nsplit, Hkv, Hq, out, part_o, part_ml, count, s_buf, &s_m[0][0],
-                              &s_l[0][0], &s_last);
+                        &s_l[0][0], &s_last);
 }
 
-int launch_decode(int dtype, const DecodeArgs& args, const void* q, const void* k, const void* v, const CacheView& cv,
-                  int layer, const float2* rope, int Hq, void* out, float* part_o, float* part_ml, int* count,
-                  hipStream_t s, KTime tm) {
+int launch_decode(const DecodeArgs& args, const void* q, const void* k, const void* v, const CacheView& cv, int layer,
+                  const float2* rope, int Hq, void* out, float* part_o, float* part_ml, int* count, hipStream_t s,
+                  KTime tm) {
   if (args.n == 0) return 0;
   const int g = Hq / cv.n_kv_heads;
   dim3 grid(args.max_split, args.n, cv.n_kv_heads);
-#define DK(T, DD, GG)                                                                                       \
-  if (cv.page_size)                                                                                         \
-    hipExtLaunchKernelGGL((decode_kernel<T, DD, GG, true>), grid, dim3(256), 0, s, tm.start, tm.stop, 0, args, (const T*)q,          \
-                       (const T*)k, (const T*)v, cv, rope, (T*)out, part_o, part_ml, count, layer);             \
-  else                                                                                                      \
-    hipExtLaunchKernelGGL((decode_kernel<T, DD, GG, false>), grid, dim3(256), 0, s, tm.start, tm.stop, 0, args, (const T*)q,         \
-                       (const T*)k, (const T*)v, cv, rope, (T*)out, part_o, part_ml, count, layer)
-#define DKG(T, DD)                                                                                          \
-  switch (g) {                                                                                              \
-    case 1: DK(T, DD, 1); break;                                                                            \
-    case 2: DK(T, DD, 2); break;                                                                            \
-    case 4: DK(T, DD, 4); break;                                                                            \
-    case 8: DK(T, DD, 8); break;                                                                            \
-    case 16: DK(T, DD, 16); break;                                                                          \
-    default: return -1;                                                                                     \
+#define DK1(DD, GG, PG)                                                                                       \
+  hipExtLaunchKernelGGL((decode_kernel<float, DD, GG, PG>), grid, dim3(256), 0, s, tm.start, tm.stop, 0, args, \
+                        (const float*)q, (const float*)k, (const float*)v, cv, rope, (float*)out, part_o,     \
+                        part_ml, count, layer)
+#define DK(DD, GG)                                                                                            \
+  if (cv.page_size) DK1(DD, GG, true);                                                                        \
+  else DK1(DD, GG, false)
+#define DKG(DD)                                                                                               \
+  switch (g) {                                                                                                \
+    case 1: DK(DD, 1); break;                                                                                 \
+    case 2: DK(DD, 2); break;                                                                                 \
+    case 4: DK(DD, 4); break;                                                                                 \
+    case 8: DK(DD, 8); break;                                                                                 \
+    case 16: DK(DD, 16); break;                                                                               \
+    default: return -1;                                                                                       \
   }
-  if (dtype == 0) { if (cv.head_dim == 64) { DKG(float, 64) } else { DKG(float, 128) } }
-  else { if (cv.head_dim == 64) { DKG(bf16_t, 64) } else { DKG(bf16_t, 128) } }
+  if (cv.head_dim == 64) { DKG(64) } else { DKG(128) }
 #undef DKG
 #undef DK
+#undef DK1
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? 0 : (int)e;
 }

@@ -121,9 +121,7 @@ __global__ void __launch_bounds__(256) decode_mfma_kernel(DecodeArgs args, const
   const int ntile = (kend - k0 + 15) >> 4;
   // the wave's n tiles are w, w + 4, ...; they pass through its own LDS ring,
   // so no barrier until the waves merge
-  
   const int n = (ntile - w + 3) >> 2;
-
   const bool new_wave = owns_new && w == (ntile & 3);  // encodes, stores and attends the new token
   char* ring = s_ring + w * (NB * TILE);
   const uint32_t ring_lds = lds_addr(ring);
@@ -381,7 +379,7 @@ __global__ void __launch_bounds__(256) decode_mfma_kernel(DecodeArgs args, const
   }
   if (nsplit == 1) return;
   merge_splits<bf16_t, D, G>(args, i, hk, slot0, nsplit, Hkv, Hq, out, part_o, part_ml, count,
-                                   reinterpret_cast<float*>(s_ring), s_mt, s_lt, &s_last);
+                             reinterpret_cast<float*>(s_ring), s_mt, s_lt, &s_last);
 }
 
 // ring: 4 where every CU has at most one block of at most 256 keys (plan_decode):

@@ -243,8 +243,8 @@ int launch_attn_rows(const AttnItem* items, int n_items, const TokenMeta* meta, 
                      const CacheView& cv, int layer, int Hq, void* out, float* part_o, float* part_ml,
                      int part_stride_rows, int tokens, hipStream_t s, KTime tm = {});
 
-// Decode step: encode + store the new token and split-KV attention over the
-// cache.  q, k, v, out: [n][H][D] rows in the order of args.seq.  Grid
+// Decode step, fp32 caches: encode + store the new token and split-KV attention
+// over the cache.  q, k, v, out: [n][H][D] rows in the order of args.seq.  Grid
 // (max_split, n, Hkv).  Splits of multi-split sequences leave partials in
 // part_o [slot][Hkv][g][D] and part_ml [slot][Hkv][g][2], slot = split0[i] +
 // split; the last block of each (sequence, kv head) to finish merges them.
@@ -252,9 +252,9 @@ int launch_attn_rows(const AttnItem* items, int n_items, const TokenMeta* meta, 
 // per 128-byte line: atomics on one line serialise), zero before the launch
 // and zero again after it.
 constexpr int kCountStride = 32;
-int launch_decode(int dtype, const DecodeArgs& args, const void* q, const void* k, const void* v, const CacheView& cv,
-                  int layer, const float2* rope, int Hq, void* out, float* part_o, float* part_ml, int* count,
-                  hipStream_t s, KTime tm = {});
+int launch_decode(const DecodeArgs& args, const void* q, const void* k, const void* v, const CacheView& cv, int layer,
+                  const float2* rope, int Hq, void* out, float* part_o, float* part_ml, int* count, hipStream_t s,
+                  KTime tm = {});
 
 // The same step on matrix cores for bf16 caches and query groups of up to 16
 // heads (same arguments; -1 for a group size it has no instance for).  ring:

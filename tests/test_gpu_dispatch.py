@@ -26,13 +26,22 @@ def test_graft_plan_by_value_and_uploaded(n_seqs, n_segs, page, alias):
     parity.run_pipeline(w, [1], 1, [0, n_seqs - 1], alias=alias)
 
 
+@pytest.mark.parametrize("page", [0, 16])
+@pytest.mark.parametrize("last", [2048, 2049])
+def test_graft_of_as_many_runs_as_go_by_value(last, page):
+    """32 segments in 1024 runs of 64 tokens go by value, one token more through the staging ring."""
+    segs = [[0, 1, 2, 3]] * 7 + [[0, 1, 2, 4]]
+    w = synth.custom(synth.Shape(1, 2, 1, 64, 1e4, "bf16"), 4, [2048] * 4 + [last], segs, 1, 1, page_size=page)
+    parity.run_pipeline(w, [0], 1, [0, 7])
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("g,page,alias", [(1, 0, False), (2, 16, True), (4, 16, False), (8, 0, False), (16, 16, True)])
 @pytest.mark.parametrize("ctx", ["edges", "long"])
 def test_decode_ring_and_merge(d, g, page, alias, ctx):
     """Both rings of the bf16 decode (one short split per CU; two blocks per CU past 256 keys for
     each) at ragged lengths: fewer tiles than waves, a partial tile, a split that holds the new
-    token alone, one sequence with splits beyond one batch of the merge's loads."""
+    token alone, a sequence of many splits."""
     if ctx == "edges":
         hkv, lens = 2, [1, 15, 63, 64, 127, 800, 191]
     else:
@@ -42,6 +51,24 @@ def test_decode_ring_and_merge(d, g, page, alias, ctx):
     w = synth.custom(synth.Shape(1, hkv * g, hkv, d, 1e6, "bf16"), 5, [max(1, n - 2) for n in lens], segs, 2, 3,
                      page_size=page)
     parity.run_pipeline(w, [0], 3, list(range(len(lens))), alias=alias)
+
+
+@pytest.mark.parametrize("g,d,ctx", [(4, 128, 2990), (2, 64, 9990), (8, 64, 4100), (16, 64, 2100)])
+@pytest.mark.parametrize("page", [0, 16])
+def test_decode_merge_in_several_batches(g, d, ctx, page):
+    """One kv head, so splits of 64 keys: more of them (47, 157, 65, 33) than the merge's lanes fetch
+    at a time (8 per lane: 32, 128, 32, 16), as many lanes to a chunk as the instance has (4, 16, 4, 2)."""
+    w = synth.custom(synth.Shape(1, g, 1, d, 1e6, "bf16"), 15, [ctx], [[0]], 1, 2, page_size=page)
+    parity.run_pipeline(w, [0], 2, [0])
+
+
+@pytest.mark.parametrize("g,d,page,alias", [(4, 128, 0, False), (16, 64, 16, True), (1, 128, 16, False)])
+def test_decode_of_many_short_sequences(g, d, page, alias):
+    """Few keys but more blocks than CUs, most of them empty (one long sequence): the ring of two."""
+    lens = [5, 33, 61, 900] + [9] * 36
+    w = synth.custom(synth.Shape(1, 2 * g, 2, d, 1e6, "bf16"), 16, lens, [[i] for i in range(len(lens))], 2, 2,
+                     page_size=page)
+    parity.run_pipeline(w, [0], 2, [0, 1, 2, 3, 39], alias=alias)
 
 
 @pytest.mark.parametrize("g,d", [(1, 64), (2, 128), (8, 64), (16, 128)])

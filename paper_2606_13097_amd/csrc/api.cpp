@@ -78,8 +78,9 @@ fcg_status upload_inv_freq(const fcg_model_desc& d, double** out) {
 }
 
 // Staging of per-call plans: a pinned host ring mirrored by a device ring.  A
-// call packs its arrays into one blob, copies it host-to-device on the call's
-// stream and records an event; a region is reused only after its event.
+// call packs its arrays into one blob, which one kernel on the call's stream
+// takes from the host ring (upload), and records an event after its last kernel;
+// a region is reused only after its event.
 struct Ring {
   char* host = nullptr;
   char* dev = nullptr;
@@ -1103,7 +1104,7 @@ fcg_status run_attention(fcg_cache* c, int32_t layer, const std::vector<TokenMet
   Blob blob;
   std::vector<std::pair<int32_t, size_t>> rows;
   stage_pages(c, new_pages, &blob, &rows);
-  // fused calls take their whole plan by value: an upload (one more copy
+  // fused calls take their whole plan by value: an upload (one more launch
   // before the kernel) only when the call maps new pages
   const bool upload_plan = !fused || !rows.empty();
   const size_t o_meta = fused ? 0 : blob.add(meta.data(), meta.size() * sizeof(TokenMeta));

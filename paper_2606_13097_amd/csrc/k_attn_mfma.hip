@@ -224,7 +224,7 @@ __global__ void __launch_bounds__(WAVES * 64, WAVES == 4 ? 2 : 1) attn_prefill_m
   // 32 paged tasks x 32 tokens 736 -> 700 us for 4 layers, 34B shape 2774 ->
   // 2678 for 2, 16.7K context 1535 -> 1515).  Not in contiguous launches of
   // 16-row waves: those are bound by latency, not by issue (7B patch: 602 us a
-  // pass with it, 595 without).
+  // pass with it, 593 without).
   constexpr bool BASED = PAGED || RT > 1;
   constexpr int RI = 64 / NC;                       // rows of one instruction
   const int lane_row = lane / NC * D * 2;           // byte offset of the lane's row in the instruction's

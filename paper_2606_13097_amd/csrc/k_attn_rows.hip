@@ -197,7 +197,7 @@ __global__ void __launch_bounds__(256) attn_rows_kernel(const AttnItem* __restri
 // PRE splits' partial outputs of the lane's 4-dim chunk; 32 lanes per
 // row then form the scales 2^(M_s - M) / L with shuffles, and each 4-dim
 // output chunk is summed over the splits (fp32 partials: LPC lanes per chunk
-// taking interleaved splits, their sums added through LDS).
+// taking interleaved splits, their sums added one by one through LDS).
 constexpr int kCombRows = 8;
 constexpr int kCombMaxParts = 256;
 // PRE: the smallest of 4, 16 and 32 that covers every row block of the
@@ -227,7 +227,7 @@ __global__ void __launch_bounds__(256) combine_kernel(CombineArgs args, const To
   auto prow = [&](int s, int r) { return ((int64_t)(it.part0 + s) * Hkv + hk) * part_stride_rows + r0 + r; };
   constexpr int CPR = D / 4;                  // 4-dim chunks per row
   const int nch = nr * CPR;
-  const int lpc = max(1, 256 / nch);          // lanes per chunk (power of two: nr, CPR are)
+  const int lpc = max(1, 256 / nch);          // lanes per chunk, consecutive (any number: 5 for three rows of 16 chunks)
   // chunk c -> (row, 4-dim chunk): neighbouring lanes read neighbouring bytes
   // (rows fastest in the MFMA fragment order, dims fastest in row-major order)
   auto chunk = [&](int c, int* r, int* c4) {

@@ -238,7 +238,9 @@ fcg_status fcg_graft(fcg_cache* cache, const fcg_lib* lib, int32_t n_items, cons
  * (rounded to storage), its key and value stored at pos[t], and
  * out[t] = softmax(q k^T / sqrt(D)) v over every position <= pos[t] of its
  * sequence, query head h reading kv head h / (Hq / Hkv).  Tokens may belong to
- * several sequences and come in any order.  q, k, v, out: device.
+ * several sequences and come in any order.  q, k, v, out: device, starting at
+ * any element (here and in the decode calls; multiples of 16 bytes take the
+ * faster loads).
  * Errors: ERANGE, EOVERLAP (position given twice or already written in this
  * layer), EHOLE (a position below a query's is unwritten after the call),
  * ENOMEM (pages). */
